@@ -62,6 +62,31 @@ void* ws_get(qmg_ctx* c, const std::string& name, size_t bytes) {
   return p;
 }
 
+void* ws_try(qmg_ctx* c, const std::string& name, size_t bytes, hipStream_t s) {
+  if (s != c->cap_stream || !s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
+  void* p = ws_get(c, name, bytes);
+  if (!p) (void)hipGetLastError();
+  return p;
+}
+
+hipError_t scratch_acquire(qmg_ctx* c, hipStream_t s) {
+  return c->scratch_ev ? hipStreamWaitEvent(s, c->scratch_ev, 0) : hipSuccess;
+}
+
+hipError_t scratch_release(qmg_ctx* c, hipStream_t s) {
+  if (!c->scratch_ev) {
+    const hipError_t e = hipEventCreateWithFlags(&c->scratch_ev, hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+  }
+  return hipEventRecord(c->scratch_ev, s);
+}
+
 void ws_release(qmg_ctx* c, const std::string& name) {
   auto it = c->ws.find(name);
   if (it == c->ws.end()) return;
@@ -271,6 +296,7 @@ qmg_status qmg_create(qmg_ctx** out, const int dims[4], const int block[4], int 
   g.bs_log = ilog2(bs);
   g.nb = nb;
   g.V = V;
+  c->b44 = block[0] == 4 && block[1] == 4 && block[2] == 4 && block[3] == 4;
   c->sap_ok = bs <= 256 && bs >= 16;
   for (int mu = 0; mu < 4; ++mu) c->sap_ok = c->sap_ok && g.nbk[mu] >= 2 && g.nbk[mu] % 2 == 0;
   // colour-major block numbering
@@ -335,6 +361,7 @@ qmg_status qmg_destroy(qmg_ctx* c) {
   hipDeviceSynchronize();
   for (auto& kv : c->graphs) hipGraphExecDestroy(kv.second);
   if (c->cap_stream) hipStreamDestroy(c->cap_stream);
+  if (c->scratch_ev) hipEventDestroy(c->scratch_ev);
   for (int p = 0; p < 3; ++p) {
     free_ptr(c->U[p]);
     free_ptr(c->Dg[p]);
@@ -486,10 +513,7 @@ qmg_status qmg_sap_smooth(qmg_ctx* c, void* x, const void* f, const double* tau,
   QMG_TRY(check_tau(c, tau, nrhs));
   if (!x || !f || x == f || nsweep < 0 || n_mr < 0) return set_err(c, QMG_E_ARG, "sap_smooth: bad arguments");
   hipSetDevice(c->device);
-  for (int sw = 0; sw < nsweep; ++sw)
-    for (int col = 0; col < 2; ++col)
-      QMG_TRY(hipchk(c, launch_sap_colour(c, p, x, f, tau, nrhs, col, n_mr, s), "sap"));
-  return QMG_OK;
+  return hipchk(c, launch_sap(c, p, x, f, tau, nrhs, nsweep, n_mr, s), "sap");
 }
 
 qmg_status qmg_set_test_vectors(qmg_ctx* c, const void* W, int ntv, hipStream_t s) {

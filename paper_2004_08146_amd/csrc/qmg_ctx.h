@@ -34,7 +34,7 @@ struct Tune {
   int dslash[3][2] = {{1, 1}, {1, 1}, {1, 1}};  // [prec][nrhs == 1 ? 0 : 1] -> variant index
   int dslash_xcd_remap = 1;                      // XCD-aware mapping of work-groups to blocks
   int force_variant = -1;                        // >= 0: use this stencil variant (tuning, tests)
-  int sap_variant = 2;  // 0 generic SAP; 1, 2: LDS-staged 4^4 SAP (FP32 / BF16) with 1 or 2 rhs per work-group
+  int sap_variant = 2;  // SAP: 0 generic kernel; 1 gathering 4^4 kernel (FP32 / BF16); 2 halo-field 4^4 kernel
   int coarse_rhs_tile = 4;                       // right-hand sides per coarse-apply work-group
   int coarse_mfma = 1;                           // MFMA coarse apply for many right-hand sides
   int transfer_mr = 1;                           // restrict / prolong kernels sharing P loads across rhs
@@ -72,6 +72,7 @@ struct qmg_ctx {
   int tile_blocks = 1;
   std::vector<int> h_nbr, h_bcoord;
   std::vector<int64_t> lex_of_block;
+  bool b44 = false;            // 4^4 blocks
   bool sap_ok = false;
   // gauge
   bool have_gauge = false;
@@ -93,6 +94,7 @@ struct qmg_ctx {
   std::map<std::string, hipGraphExec_t> graphs;  // captured V-cycles by (buffers, shifts, parameters)
   uint64_t ws_epoch = 0;                          // bumped whenever a workspace buffer moves
   hipStream_t cap_stream = nullptr;               // library stream used only to record graphs
+  hipEvent_t scratch_ev = nullptr;                // end of the last call that used the scratch of ws_try
   double* noalloc_scratch = nullptr;              // device address of this device's no-allocation scratch
 };
 
@@ -105,6 +107,14 @@ qmg_status set_ds_order(qmg_ctx* c, int order);
 
 // named, lazily grown device workspace (never shrinks; freed by qmg_destroy)
 void* ws_get(qmg_ctx* c, const std::string& name, size_t bytes);
+// Scratch that a call can do without (nullptr: go the way that needs none): as ws_get,
+// but a failed allocation leaves no HIP error behind, and a caller's own stream capture
+// gets none, since a later call may move the buffer under the captured graph.
+void* ws_try(qmg_ctx* c, const std::string& name, size_t bytes, hipStream_t s);
+// Calls on different streams share the scratch: a call's kernels wait for those of the
+// call before it (an event; a recorded V-cycle is bracketed where it is launched).
+hipError_t scratch_acquire(qmg_ctx* c, hipStream_t s);
+hipError_t scratch_release(qmg_ctx* c, hipStream_t s);
 void ws_release(qmg_ctx* c, const std::string& name);
 void drop_graphs(qmg_ctx* c);
 
@@ -122,10 +132,13 @@ hipError_t launch_dslash(const qmg_ctx* c, int p, void* out, const void* in, con
 // (D - tau Gamma5) in FP64 arithmetic and storage, reading an input field stored in in_prec
 hipError_t launch_dslash_d_in(const qmg_ctx* c, void* out, const void* in, int in_prec, const double* tau,
                               int nrhs, hipStream_t s, int mode = 0);
+// ---- sap44.hip (4^4 blocks): nsweep SAP sweeps; done: false when the scratch fields do not fit in memory
+hipError_t launch_sap44(qmg_ctx* c, int p, void* x, const void* f, const double* tau, int nrhs, int nsweep, int n_mr,
+                        hipStream_t s, int qform, bool* done);
 // ---- sap.hip
-// qform: SAP for Q - tau = Gamma5 A_tau itself instead of A_tau
-hipError_t launch_sap_colour(const qmg_ctx* c, int p, void* x, const void* f, const double* tau,
-                             int nrhs, int colour, int n_mr, hipStream_t s, int qform = 0);
+// nsweep red-black sweeps on A_tau x = f; qform: on Q - tau = Gamma5 A_tau itself
+hipError_t launch_sap(qmg_ctx* c, int p, void* x, const void* f, const double* tau, int nrhs, int nsweep, int n_mr,
+                      hipStream_t s, int qform = 0);
 // ---- transfer.hip
 hipError_t launch_build_P(const qmg_ctx* c, void* P64, const void* W, int ntv, int* d_fail,
                           hipStream_t s);

@@ -329,7 +329,9 @@ qmg_status solver_vcycle(qmg_ctx* c, void* z, const void* r, const double* tau, 
   if (coarse_iters && prm->use_coarse && c->have_mg) *coarse_iters += prm->coarse_maxiter;
   auto it = c->graphs.find(key);
   if (it != c->graphs.end()) {
-    hipError_t e = hipGraphLaunch(it->second, s);
+    hipError_t e = scratch_acquire(c, s);
+    if (e == hipSuccess) e = hipGraphLaunch(it->second, s);
+    if (e == hipSuccess) e = scratch_release(c, s);
     return e == hipSuccess ? QMG_OK : hip_err(c, e, "graph launch");
   }
   // first use: run eagerly on the caller's stream (this also sizes every
@@ -427,11 +429,8 @@ static qmg_status vcycle_body(qmg_ctx* c, void* z, const void* r, const double* 
     e = launch_add(p, zp, ez, n, n, nrhs, s);
     if (e != hipSuccess) return hip_err(c, e, "smoother update");
   } else {
-    for (int sw = 0; sw < prm->nu_post; ++sw)
-      for (int col = 0; col < 2; ++col) {
-        e = launch_sap_colour(c, p, zp, rp, tau, nrhs, col, prm->n_mr, s, prm->q_form);
-        if (e != hipSuccess) return hip_err(c, e, "sap");
-      }
+    e = launch_sap(c, p, zp, rp, tau, nrhs, prm->nu_post, prm->n_mr, s, prm->q_form);
+    if (e != hipSuccess) return hip_err(c, e, "sap");
   }
   if (p != QMG_F64 && zprec != p) {
     e = launch_convert(z, QMG_F64, zp, p, n * nrhs, s);
@@ -752,11 +751,8 @@ qmg_status solver_setup(qmg_ctx* c, void* W, int ntv, int iters, int smooth, int
   if (!zero) return set_err(c, QMG_E_NOMEM, "out of device memory (setup)");
   hipError_t e = launch_fill_zero(zero, fb * ntv, s);
   if (e != hipSuccess) return hip_err(c, e, "zero");
-  for (int sw = 0; sw < smooth; ++sw)
-    for (int col = 0; col < 2; ++col) {
-      e = launch_sap_colour(c, QMG_F64, W, zero, tau0.data(), ntv, col, n_mr, s);
-      if (e != hipSuccess) return hip_err(c, e, "setup sap");
-    }
+  e = launch_sap(c, QMG_F64, W, zero, tau0.data(), ntv, smooth, n_mr, s);
+  if (e != hipSuccess) return hip_err(c, e, "setup sap");
   auto normalise = [&](void* X) -> qmg_status {
     std::vector<double> nn;
     qmg_status st = sp.norms(nn, X);

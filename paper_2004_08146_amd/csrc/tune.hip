@@ -203,7 +203,7 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
       js << ",\n  \"" << key << "|ds_order\": " << best_o << ",\n  \"" << key << "|ds_order|ms\": [" << ot.str()
          << "]";
   }
-  // SAP kernel choice (FP32 arithmetic paths), one colour half-sweep on 16 rhs
+  // SAP kernel choice (FP32 arithmetic paths), the three sweeps of a V-cycle on 16 rhs
   const int sap_default = c->tune.sap_variant;
   for (int p = 1; p < 3 && st == QMG_OK && c->sap_ok && b44; ++p) {
     const int n = 16;
@@ -218,9 +218,9 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
     std::ostringstream times;
     for (int v = 0; v < 3 && e == hipSuccess; ++v) {
       c->tune.sap_variant = v;
-      e = launch_sap_colour(c, p, x, f, tau.data(), n, 0, 3, s);
+      e = launch_sap(c, p, x, f, tau.data(), n, 3, 3, s);
       if (e == hipSuccess) e = hipEventRecord(e0, s);
-      for (int r = 0; r < 3 && e == hipSuccess; ++r) e = launch_sap_colour(c, p, x, f, tau.data(), n, 0, 3, s);
+      for (int r = 0; r < 3 && e == hipSuccess; ++r) e = launch_sap(c, p, x, f, tau.data(), n, 3, 3, s);
       if (e == hipSuccess) e = hipEventRecord(e1, s);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0.f;
