@@ -1,4 +1,4 @@
-// Galerkin coarse operator D_c = P^H D P (Sec. 2) and its application
+// Application of the Galerkin coarse operator D_c = P^H D P (Sec. 2):
 // out_k = (D_c - tau_k Gamma5^c) in_k.
 //
 // D_c couples each coarse site (lattice block) b to itself and to its 8
@@ -7,11 +7,7 @@
 // eq. (2.9)), so Gamma5^c D_c Gamma5^c = D_c^H and, hop type by hop type, the
 // block coupling b to X - mu is Gamma5^c (the block coupling X - mu to b)^H
 // Gamma5^c.  The apply kernels rebuild those backward blocks on the fly.
-// D_c is assembled column by column, a batch of columns at a time: prolong
-// unit coarse vectors, split D applied to each into the block-local part
-// (diagonal plus hops inside the block) and the 4 forward hop parts that leave
-// the block, restrict all parts as one multi-rhs restriction (each part with
-// the receiving block's P) and scatter them into the blocks.  Blocks are
+// Blocks are
 // stored transposed, DcT[b][e][j][i] = D_c[b][e]_{ij}, e = 0 self, 1 + mu for
 // the block at X + mu (kept apart from the -mu coupling even when the two
 // neighbours coincide).  In the 9-entry stencil numbering used by the kernels,
@@ -21,62 +17,6 @@
 #include "qmg_ctx.h"
 
 namespace {
-
-// out5[0] = block-local part (diagonal, clover and the hops that stay inside
-// the block), out5[1 + mu] = forward hop leaving the block (zero where it stays
-// inside); the backward hops that leave the block are not needed
-__global__ __launch_bounds__(256) void k_split(Geom g, double2* out5, const double2* in, const double2* U,
-                                               const double2* diag, double mass4, int clover) {
-  int64_t site = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (site >= g.V) return;
-  const int b = (int)(site >> g.bs_log), l = (int)(site & ((1 << g.bs_log) - 1));
-  const int64_t fs = g.V * 12;
-  Spinor<double> self = load_spinor<double>(in, g, b, l);
-  Spinor<double> loc0;
-  if (clover) loc0 = apply_diag<double>(diag, g, b, l, self);
-  else
-    for (int s = 0; s < 4; ++s)
-      for (int c = 0; c < 3; ++c) loc0.s[s][c] = mass4 * self.s[s][c];
-  for (int mu = 0; mu < 4; ++mu) {
-    for (int dir = 0; dir < 2; ++dir) {
-      const bool fwd = dir == 0;
-      int bn, ln;
-      if (fwd) nb_fwd(g, b, l, mu, bn, ln);
-      else nb_bwd(g, b, l, mu, bn, ln);
-      Half<double> h = project(load_spinor<double>(in, g, bn, ln), mu, fwd);
-      Half<double> w = fwd ? umul(load_link<double>(U, g, b, mu, l), h)
-                           : udagmul(load_link<double>(U, g, bn, mu, ln), h);
-      Spinor<double> t;
-      for (int s = 0; s < 4; ++s)
-        for (int c = 0; c < 3; ++c) t.s[s][c] = czero<double>();
-      accum_recon(t, w, mu, fwd);
-      const bool inside = fwd ? (loc(g, l, mu) < g.msk[mu]) : (loc(g, l, mu) > 0);
-      for (int s = 0; s < 4; ++s)
-        for (int c = 0; c < 3; ++c)
-          if (inside) loc0.s[s][c] = loc0.s[s][c] - 0.5 * t.s[s][c];
-      if (fwd) {
-        Spinor<double> o;
-        for (int s = 0; s < 4; ++s)
-          for (int c = 0; c < 3; ++c) o.s[s][c] = inside ? czero<double>() : (-0.5) * t.s[s][c];
-        store_spinor(out5 + (1 + mu) * fs, g, b, l, o);
-      }
-    }
-  }
-  store_spinor(out5, g, b, l, loc0);
-}
-
-// DcT[b][e][c0 + kk][i] = part[kk * 5 + e][b][i]: restricted stencil parts of a
-// batch of kb unit columns into the transposed blocks of D_c
-__global__ __launch_bounds__(256) void k_scatter_dc(double2* DcT, const double2* part, int nb, int nc, int c0,
-                                                  int64_t total) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int i = (int)(idx % nc);
-  const int64_t t = idx / nc;
-  const int b = (int)(t % nb), n = (int)(t / nb);
-  const int kk = n / 5, e = n - 5 * kk;
-  DcT[(((int64_t)b * 5 + e) * nc + c0 + kk) * nc + i] = part[idx];
-}
 
 struct TauArr {
   double t[QMG_MAXRHS];
@@ -296,21 +236,6 @@ void capply_s(const qmg_ctx* c, const CLevel& lv, int p, void* out, const void* 
 }
 
 }  // namespace
-
-hipError_t launch_split_stencil(const qmg_ctx* c, void* out5, const void* in, hipStream_t s) {
-  hipLaunchKernelGGL(k_split, dim3((unsigned)((c->g.V + 255) / 256)), dim3(256), 0, s, c->g, (double2*)out5,
-                     (const double2*)in, (const double2*)c->U[QMG_F64], (const double2*)c->Dg[QMG_F64],
-                     c->m0 + 4.0, c->clover ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter_dc(const qmg_ctx* c, void* Dc64, const void* part, int c0, int kb, hipStream_t s) {
-  const int nc = 2 * c->ntv;
-  const int64_t total = (int64_t)kb * 5 * c->g.nb * nc;
-  hipLaunchKernelGGL(k_scatter_dc, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (double2*)Dc64,
-                     (const double2*)part, c->g.nb, nc, c0, total);
-  return hipGetLastError();
-}
 
 // tau: host array of nrhs shifts
 hipError_t launch_coarse_apply(const qmg_ctx* c, int p, void* out, const void* in, const double* dtau, int nrhs,

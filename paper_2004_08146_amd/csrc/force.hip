@@ -47,22 +47,10 @@ __global__ __launch_bounds__(256) void k_force(Geom g, double2* G, double2* Gb, 
   }
 }
 
-__global__ void k_unit_coarse(double2* y, int nb, int nc, int col) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)nb * nc) return;
-  y[i] = make_double2((i % nc) == col ? 1.0 : 0.0, 0.0);
-}
-
 }  // namespace
 
 hipError_t launch_force(const qmg_ctx* c, double* dU, double* dUb, const void* phi, const void* x, hipStream_t s) {
   hipLaunchKernelGGL(k_force, dim3((unsigned)((c->g.V + 255) / 256)), dim3(256), 0, s, c->g, (double2*)dU,
                      (double2*)dUb, (const double2*)phi, (const double2*)x);
-  return hipGetLastError();
-}
-
-hipError_t launch_unit_coarse(void* y, int nb, int nc, int col, hipStream_t s) {
-  const int64_t n = (int64_t)nb * nc;
-  hipLaunchKernelGGL(k_unit_coarse, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (double2*)y, nb, nc, col);
   return hipGetLastError();
 }

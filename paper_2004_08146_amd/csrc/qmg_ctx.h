@@ -140,14 +140,18 @@ hipError_t launch_sap44(qmg_ctx* c, int p, void* x, const void* f, const double*
 hipError_t launch_sap(qmg_ctx* c, int p, void* x, const void* f, const double* tau, int nrhs, int nsweep, int n_mr,
                       hipStream_t s, int qform = 0);
 // ---- transfer.hip
-hipError_t launch_build_P(const qmg_ctx* c, void* P64, const void* W, int ntv, int* d_fail,
-                          hipStream_t s);
+// all three storage types of c->P
+hipError_t launch_build_P(const qmg_ctx* c, const void* W, int ntv, int* d_fail, hipStream_t s);
 hipError_t launch_restrict(const qmg_ctx* c, int p, void* yc, const void* v, int nrhs, hipStream_t s);
 hipError_t launch_prolong(const qmg_ctx* c, int p, void* v, const void* yc, int nrhs, hipStream_t s);
+// ---- galerkin.hip: FP64 D_c from P
+// out[kk] = block-local part of D applied to column c0 + kk of P, kk < kb (fields)
+hipError_t launch_self_part(const qmg_ctx* c, void* out, int c0, int kb, hipStream_t s);
+// self blocks of those columns from their restrictions part[kk][b][:]
+hipError_t launch_scatter_self(const qmg_ctx* c, const void* part, int c0, int kb, hipStream_t s);
+// the four forward blocks of every coarse site
+hipError_t launch_face_part(const qmg_ctx* c, hipStream_t s);
 // ---- coarse.hip
-hipError_t launch_split_stencil(const qmg_ctx* c, void* out9, const void* in, hipStream_t s);
-// DcT[b][d][c0 + kk][:] = part[kk * 9 + d][b][:] for kk < kb (restricted parts, FP64)
-hipError_t launch_scatter_dc(const qmg_ctx* c, void* Dc64, const void* part, int c0, int kb, hipStream_t s);
 hipError_t launch_coarse_apply(const qmg_ctx* c, int p, void* out, const void* in, const double* tau,
                                int nrhs, hipStream_t s, int qform = 0);  // tau: host array
 // level-3 operator A3(tau) = D3 - tau Gamma5^cc on level-3 vectors of the coarse precision of p
@@ -188,7 +192,6 @@ hipError_t launch_multidot_shared(int p, double* dots, const void* V, int64_t vs
 hipError_t launch_fill_zero(void* y, size_t bytes, hipStream_t s);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // ---- force.hip
-hipError_t launch_unit_coarse(void* y, int nb, int nc, int col, hipStream_t s);
 hipError_t launch_force(const qmg_ctx* c, double* dU, double* dUb, const void* phi, const void* x,
                         hipStream_t s);
 

@@ -16,6 +16,7 @@
 //   three sweeps, 48x24^3, BF16, 2 right-hand sides    1.32 -> 0.96 ms
 //   four sweeps, 24x16^3, FP64, 24 right-hand sides    7.35 -> 4.42 ms
 #include "qmg_ctx.h"
+#include "reduce.h"
 
 namespace {
 
@@ -72,28 +73,6 @@ __device__ __forceinline__ uint32_t site_of(uint32_t j, uint32_t v) {
   else if constexpr (MU == 1) return ((j >> 4) << 6) | (v << 4) | (j & 15u);
   else if constexpr (MU == 2) return ((j >> 2) << 4) | (v << 2) | (j & 3u);
   else return (j << 2) | v;
-}
-
-// sum over the 64 lanes, in lane 63 (row shifts, then row broadcasts: fixed order)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xf, true));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const uint64_t u = __double_as_longlong(v);
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)u, CTRL, ROWS, 0xf, true);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
-  return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-template <typename R>
-__device__ __forceinline__ R wave_sum63(R v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  v = dpp_add<0x142, 0xa>(v);
-  return dpp_add<0x143, 0xc>(v);
 }
 
 // LDS of a work-group: -1/2 U of directions 1..3 and the vector that the block operator

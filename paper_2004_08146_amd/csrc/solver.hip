@@ -700,36 +700,30 @@ qmg_status build_mg(qmg_ctx* c, const void* W, int ntv, hipStream_t s) {
   int* fail = (int*)ws_get(c, "mg_fail", sizeof(int));
   if (!fail) return set_err(c, QMG_E_NOMEM, "out of device memory");
   hipError_t e = hipMemsetAsync(fail, 0, sizeof(int), s);
-  if (e == hipSuccess) e = launch_build_P(c, c->P[QMG_F64], W, ntv, fail, s);
+  if (e == hipSuccess) e = launch_build_P(c, W, ntv, fail, s);
   int hfail = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(&hfail, fail, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_err(c, e, "build P");
   if (hfail) return set_err(c, QMG_E_NUMERIC, "test vectors are locally rank deficient");
-  // D_c column by column, kb columns per batch (workspace capped near 8 GiB):
-  // one multi-rhs prolongation and one multi-rhs restriction per batch read P
-  // once per 16 right-hand sides instead of once per part
+  // D_c: the forward blocks straight from P and the links; the self block kb columns at a
+  // time (workspace capped near 8 GiB), restricted as one batch of right-hand sides
   const size_t fb = field_elems(c) * 16, cb = coarse_elems(c) * 16;
-  const int K = (int)std::max<size_t>(1, std::min<size_t>((size_t)nc, ((size_t)8 << 30) / (6 * fb)));
-  void* ycol = ws_get(c, "mg_ycol", cb * K);
-  void* pcol = ws_get(c, "mg_pcol", fb * K);
-  void* five = ws_get(c, "mg_five", fb * 5 * K);
-  void* part = ws_get(c, "mg_part", cb * 5 * K);
-  if (!ycol || !pcol || !five || !part) return set_err(c, QMG_E_NOMEM, "out of device memory (D_c assembly)");
-  for (int c0 = 0; c0 < nc; c0 += K) {
+  const int K = (int)std::max<size_t>(1, std::min<size_t>((size_t)nc, ((size_t)8 << 30) / fb));
+  void* self = ws_get(c, "mg_self", fb * K);
+  void* part = ws_get(c, "mg_part", cb * K);
+  if (!self || !part) return set_err(c, QMG_E_NOMEM, "out of device memory (D_c assembly)");
+  e = launch_face_part(c, s);
+  for (int c0 = 0; c0 < nc && e == hipSuccess; c0 += K) {
     const int kb = std::min(K, nc - c0);
-    for (int kk = 0; kk < kb && e == hipSuccess; ++kk) e = launch_unit_coarse((char*)ycol + kk * cb, g.nb, nc, c0 + kk, s);
-    if (e == hipSuccess) e = launch_prolong(c, QMG_F64, pcol, ycol, kb, s);
-    for (int kk = 0; kk < kb && e == hipSuccess; ++kk)
-      e = launch_split_stencil(c, (char*)five + (size_t)kk * 5 * fb, (char*)pcol + (size_t)kk * fb, s);
-    if (e == hipSuccess) e = launch_restrict(c, QMG_F64, part, five, 5 * kb, s);
-    if (e == hipSuccess) e = launch_scatter_dc(c, c->Dc[QMG_F64], part, c0, kb, s);
-    if (e != hipSuccess) return hip_err(c, e, "assemble D_c");
+    e = launch_self_part(c, self, c0, kb, s);
+    if (e == hipSuccess) e = launch_restrict(c, QMG_F64, part, self, kb, s);
+    if (e == hipSuccess) e = launch_scatter_self(c, part, c0, kb, s);
   }
+  if (e != hipSuccess) return hip_err(c, e, "assemble D_c");
   for (int p = 1; p < 3; ++p) {
-    e = launch_convert(c->P[p], p, c->P[QMG_F64], QMG_F64, (int64_t)pel, s);
-    if (e == hipSuccess) e = launch_convert(c->Dc[p], p, c->Dc[QMG_F64], QMG_F64, (int64_t)del, s);
-    if (e != hipSuccess) return hip_err(c, e, "convert P/D_c");
+    e = launch_convert(c->Dc[p], p, c->Dc[QMG_F64], QMG_F64, (int64_t)del, s);
+    if (e != hipSuccess) return hip_err(c, e, "convert D_c");
   }
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_err(c, e, "sync");
@@ -789,7 +783,6 @@ qmg_status solver_setup(qmg_ctx* c, void* W, int ntv, int iters, int smooth, int
   }
   ws_release(c, "su_zero");
   ws_release(c, "su_new");
-  ws_release(c, "mg_five");
-  ws_release(c, "mg_pcol");
+  ws_release(c, "mg_self");
   return QMG_OK;
 }
