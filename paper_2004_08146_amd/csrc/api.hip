@@ -204,7 +204,6 @@ qmg_status set_ds_order(qmg_ctx* c, int order) {
     return set_err(c, QMG_E_NOMEM, "stencil order table");
   hipError_t e = hipMemcpy(c->d_tord, tord.data(), sizeof(int) * (size_t)g.nb, hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_err(c, e, "stencil order table");
-  c->tile_blocks = T[0] * T[1] * T[2] * T[3];
   c->tune.ds_order = order;
   return QMG_OK;
 }

@@ -25,8 +25,8 @@ struct DsArgs {
   int64_t fstride;  // complex elements per field
   int nrhs;
   int remap;
-  const int* tord;  // block ids in work order: tiles of tb blocks, each tile's rhs groups back to back
-  int tb;
+  const int* tord;  // block ids in work order
+  int per, ngrp;    // k_dslash44l: right-hand sides per work-group, work-groups per block
   int nt_out;       // 1: the output is written with non-temporal stores (streamed past the caches)
   Geom g;
   double tau[QMG_MAXRHS];
@@ -107,10 +107,7 @@ __global__ __launch_bounds__(256) void k_dslash(DsArgs<S, SI> a) {
   store_spinor(out, g, b, l, o);
 }
 
-// ---- 4^4 blocks: compile-time geometry, 32-bit offsets, R right-hand sides per
-// thread sharing every link load.  One work-group = one block x R rhs.
-template <int MU> struct Sh44 { static constexpr int v = 6 - 2 * MU; };
-
+// ---- 4^4 blocks: compile-time geometry, 32-bit offsets.
 template <typename C, typename P>
 __device__ __forceinline__ Spinor<C> ld_spinor44(const P* f, uint32_t b, uint32_t l) {
   Spinor<C> p;
@@ -136,121 +133,303 @@ __device__ __forceinline__ Link<C> ld_link44(const P* U, uint32_t b, int mu, uin
   return u;
 }
 
-// one hop (HOP = 2 mu for x + mu, 2 mu + 1 for x - mu) for R right-hand sides
-template <typename C, int HOP, int R, typename PI, typename P>
-__device__ __forceinline__ void hop44(Spinor<C> (&acc)[R], const PI* const (&in)[R], const P* U, const int* nbr,
-                                      uint32_t b, uint32_t l, int nr) {
-  constexpr int MU = HOP / 2;
-  constexpr bool FWD = (HOP % 2) == 0;
-  constexpr int SH = Sh44<MU>::v;
-  const uint32_t lc = (l >> SH) & 3u;
-  const uint32_t bo = (uint32_t)nbr[b * 8 + HOP];
-  uint32_t bn, ln;
-  if (FWD) {
-    bn = lc < 3u ? b : bo;
-    ln = lc < 3u ? l + (1u << SH) : l - (3u << SH);
-  } else {
-    bn = lc > 0u ? b : bo;
-    ln = lc > 0u ? l - (1u << SH) : l + (3u << SH);
-  }
-  const Link<C> u = FWD ? ld_link44<C>(U, b, MU, l) : ld_link44<C>(U, bn, MU, ln);
+// (m0 + 4 + C) psi with the two Hermitian 6x6 blocks of (b, l)
+template <typename C, typename P>
+__device__ __forceinline__ Spinor<C> diag44(const P* D, uint32_t b, uint32_t l, const Spinor<C>& p) {
+  Spinor<C> o;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (r < nr) {
-      const Half<C> h = project(ld_spinor44<C>(in[r], bn, ln), MU, FWD);
-      accum_recon(acc[r], FWD ? umul(u, h) : udagmul(u, h), MU, FWD);
+  for (int h = 0; h < 2; ++h) {
+    cpx<C> v[6], w[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) v[i] = p.s[2 * h + i / 3][i % 3];
+    auto ld = [&](int k) {
+      const auto d = cv(ldo(D, ((b * 36u + (uint32_t)(18 * h + k)) << 8) + l));
+      return cpx<C>{C(d.re), C(d.im)};
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const cpx<C> d = ld(k);
+      w[2 * k] = d.re * v[2 * k];
+      w[2 * k + 1] = d.im * v[2 * k + 1];
     }
-    __builtin_amdgcn_sched_barrier(0);
+    int k = 3;
+#pragma unroll
+    for (int i = 1; i < 6; ++i)
+#pragma unroll
+      for (int j = 0; j < i; ++j) {
+        const cpx<C> a = ld(k);
+        ++k;
+        w[i] = w[i] + a * v[j];
+        w[j] = w[j] + cmul_conj(a, v[i]);
+      }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) o.s[2 * h + i / 3][i % 3] = w[i];
   }
+  return o;
 }
 
-template <typename S, bool CLOVER, int MODE, int R, int W, bool LOOP, typename SI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W > 0 ? W : 1))) void k_dslash44(DsArgs<S, SI> a) {
+// ---- 4^4 blocks, each link loaded once per right-hand side.  A work-group is a block; for one direction at a
+// time every site writes to LDS the two half spinors its neighbours need, (1 - gamma) psi
+// for the site behind it and U^H (1 + gamma) psi for the site before it, and reads its own
+// two.  A site on a face has no reader inside the block for one of them; its place is taken
+// by the one that enters from the neighbour block across the same face, so that the reads
+// wrap around inside the block.  Wave w forms those of direction w, one lane per face site,
+// from the neighbours' spinors before the first direction.  One thread per site gathering
+// its 8 neighbours and links, as before, asked L2 for 2.3 KB per site and right-hand side
+// in FP32 (here 1.0 KB, 0.7 without the clover term), which is what bounded it; this is
+// bound by the lines of the faces and by HBM.  64x32^3 with clover, against the best of
+// eleven gathering variants: FP64 1 rhs 0.754 -> 0.670 ms, 16 rhs 8.68 -> 6.22; FP32 1 rhs
+// 0.403 -> 0.349, 16 rhs 4.94 -> 3.21; BF16 16 rhs 3.10 -> 2.25.
+constexpr int kL44Sh[4] = {6, 4, 2, 0};
+template <int MU>
+__device__ __forceinline__ uint32_t l44_site(uint32_t j, uint32_t v) {
+  if constexpr (MU == 0) return (v << 6) | j;
+  else if constexpr (MU == 1) return ((j >> 4) << 6) | (v << 4) | (j & 15u);
+  else if constexpr (MU == 2) return ((j >> 2) << 4) | (v << 2) | (j & 3u);
+  else return (j << 2) | v;
+}
+
+template <typename C, int MU, typename PI, typename P>
+__device__ __forceinline__ void l44_face_link(Link<C>& u, const P* U, const int* nbr, uint32_t b, uint32_t j) {
+  u = ld_link44<C>(U, (uint32_t)nbr[b * 8 + 2 * MU + 1], MU, l44_site<MU>(j, 3));
+}
+// half spinors that enter the block across direction MU at face site j
+template <typename C, int MU, typename PI>
+__device__ __forceinline__ void l44_face(Half<C>& fh, Half<C>& fw, const PI* in, const Link<C>& u, const int* nbr,
+                                         uint32_t b, uint32_t j) {
+  const Spinor<C> pf = ld_spinor44<C>(in, (uint32_t)nbr[b * 8 + 2 * MU], l44_site<MU>(j, 0));
+  const Spinor<C> pb = ld_spinor44<C>(in, (uint32_t)nbr[b * 8 + 2 * MU + 1], l44_site<MU>(j, 3));
+  fh = project(pf, MU, true);
+  fw = udagmul(u, project(pb, MU, false));
+}
+
+// the values are formed here: left to itself the compiler defers a direction's sums to the
+// end and keeps their terms in registers instead
+template <typename C>
+__device__ __forceinline__ void pin(Spinor<C>& p) {
+#pragma unroll
+  for (int i = 0; i < 12; ++i) asm volatile("" : "+v"(p.s[i / 3][i % 3].re), "+v"(p.s[i / 3][i % 3].im));
+}
+
+template <typename C, int MU, bool TWO>
+__device__ __forceinline__ void l44_dir(Spinor<C>& acc, const Spinor<C>& psi, const Link<C>& u, const Half<C>& fh,
+                                        const Half<C>& fw, cpx<C>* hb, cpx<C>* wb, uint32_t wave, uint32_t lane,
+                                        uint32_t l) {
+  constexpr int SH = kL44Sh[MU];
+  const uint32_t lc = (l >> SH) & 3u;
+  if (!TWO) __syncthreads();  // the buffers of the direction before are read
+  if (lc != 0u) {
+    const Half<C> h = project(psi, MU, true);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) hb[i * 256 + l] = h.h[i / 3][i % 3];
+  }
+  {
+    const Half<C> w = udagmul(u, project(psi, MU, false));
+    if (lc != 3u)
+#pragma unroll
+      for (int i = 0; i < 6; ++i) wb[i * 256 + l] = w.h[i / 3][i % 3];
+  }
+  if (wave == MU) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      hb[i * 256 + l44_site<MU>(lane, 0)] = fh.h[i / 3][i % 3];
+      wb[i * 256 + l44_site<MU>(lane, 3)] = fw.h[i / 3][i % 3];
+    }
+  }
+  __syncthreads();
+  const uint32_t lf = lc == 3u ? l - (3u << SH) : l + (1u << SH), lb = lc == 0u ? l + (3u << SH) : l - (1u << SH);
+  Half<C> h, w;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) h.h[i / 3][i % 3] = hb[i * 256 + lf];
+  accum_recon(acc, umul(u, h), MU, true);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) w.h[i / 3][i % 3] = wb[i * 256 + lb];
+  accum_recon(acc, w, MU, false);
+  pin(acc);
+}
+
+// HOLD: the links stay in registers over the work-group's right-hand sides
+template <typename S, bool CLOVER, int MODE, typename SI, bool HOLD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_dslash44l(DsArgs<S, SI> a) {
   using C = typename PT<S>::real;
   using P = typename PT<S>::stor;
+  using PI = typename PT<SI>::stor;
+  constexpr bool TWO = !std::is_same<C, double>::value;  // two buffers: one barrier per direction
+  __shared__ cpx<C> buf[(TWO ? 4 : 2) * 6 * 256];
   const int w = blockIdx.x, nw = gridDim.x;
   const int L = (a.remap && (nw & 7) == 0) ? (w & 7) * (nw >> 3) + (w >> 3) : w;
-  const int ng = (a.nrhs + R - 1) / R;
-  // blocks are visited in lexicographic order so that neighbouring blocks run
-  // close together in time (and, with the XCD remap, on the same XCD).  With
-  // LOOP one work-group walks all rhs groups of its block, so the block's
-  // links are fetched from HBM once and re-read from cache.
-  // Without LOOP, work-group L takes rhs group kg of one block, in tiles of tb
-  // blocks whose rhs groups run back to back (tb = 1: one block at a time).
-  uint32_t b;
-  int kbeg, kend;
-  if (LOOP) {
-    b = (uint32_t)__builtin_amdgcn_readfirstlane(a.g.lexord[L]);
-    kbeg = 0;
-    kend = ng;
-  } else {
-    const int per = a.tb * ng, ti = L / per, rem = L - ti * per;
-    kbeg = rem / a.tb;
-    kend = kbeg + 1;
-    b = (uint32_t)__builtin_amdgcn_readfirstlane(a.tord[ti * a.tb + (rem - kbeg * a.tb)]);
+  const int grp = L % a.ngrp;
+  const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(a.tord[L / a.ngrp]);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t l = threadIdx.x;
+  const int* nbr = a.g.nbr;
+  Link<C> u[HOLD ? 4 : 1], uf;
+  auto face_link = [&](uint32_t j) {
+    if (wave == 0) l44_face_link<C, 0, PI>(uf, a.U, nbr, b, j);
+    else if (wave == 1) l44_face_link<C, 1, PI>(uf, a.U, nbr, b, j);
+    else if (wave == 2) l44_face_link<C, 2, PI>(uf, a.U, nbr, b, j);
+    else l44_face_link<C, 3, PI>(uf, a.U, nbr, b, j);
+  };
+  if constexpr (HOLD) {
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) u[mu] = ld_link44<C>(a.U, b, mu, l);
+    face_link(l & 63u);
   }
-  const uint32_t l = threadIdx.x;
+  const int kend = min(a.nrhs, (grp + 1) * a.per);
 #pragma unroll 1
-  for (int kg = kbeg; kg < kend; ++kg) {
-  const int k0 = kg * R;
-  const int nr = a.nrhs - k0 < R ? a.nrhs - k0 : R;
-  const typename PT<SI>::stor* in[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) in[r] = a.in + (size_t)(k0 + (r < nr ? r : 0)) * a.fstride;
-  Spinor<C> acc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int k = grp * a.per; k < kend; ++k) {
+    asm volatile("" : "+v"(l));  // addresses are formed anew, not kept in registers
+    const uint32_t lane = l & 63u;
+    const PI* in = a.in + (size_t)k * a.fstride;
+    const Spinor<C> psi = ld_spinor44<C>(in, b, l);
+    Half<C> fh, fw;
+    if constexpr (!HOLD) face_link(lane);
+    if (wave == 0) l44_face<C, 0>(fh, fw, in, uf, nbr, b, lane);
+    else if (wave == 1) l44_face<C, 1>(fh, fw, in, uf, nbr, b, lane);
+    else if (wave == 2) l44_face<C, 2>(fh, fw, in, uf, nbr, b, lane);
+    else l44_face<C, 3>(fh, fw, in, uf, nbr, b, lane);
+    Spinor<C> acc;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) acc[r].s[s][c] = czero<C>();
-#pragma unroll 1
-  for (int hop = 0; hop < 8; ++hop) {
-    switch (hop) {
-      case 0: hop44<C, 0, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 1: hop44<C, 1, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 2: hop44<C, 2, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 3: hop44<C, 3, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 4: hop44<C, 4, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 5: hop44<C, 5, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      case 6: hop44<C, 6, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-      default: hop44<C, 7, R>(acc, in, a.U, a.g.nbr, b, l, nr); break;
-    }
-  }
+      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
+    cpx<C>*h0 = buf, *w0 = buf + 6 * 256, *h1 = TWO ? buf + 12 * 256 : h0, *w1 = TWO ? buf + 18 * 256 : w0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (r >= nr) break;
-    const Spinor<C> self = ld_spinor44<C>(in[r], b, l);
+    for (int mu = 0; mu < 4; ++mu) {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" : "+v"(l));
+      if constexpr (!HOLD) u[0] = ld_link44<C>(a.U, b, mu, l);
+      switch (mu) {
+        case 0: l44_dir<C, 0, TWO>(acc, psi, u[0], fh, fw, h0, w0, wave, lane, l); break;
+        case 1: l44_dir<C, 1, TWO>(acc, psi, u[HOLD ? 1 : 0], fh, fw, h1, w1, wave, lane, l); break;
+        case 2: l44_dir<C, 2, TWO>(acc, psi, u[HOLD ? 2 : 0], fh, fw, h0, w0, wave, lane, l); break;
+        default: l44_dir<C, 3, TWO>(acc, psi, u[HOLD ? 3 : 0], fh, fw, h1, w1, wave, lane, l); break;
+      }
+    }
     Spinor<C> o;
-    if (CLOVER) {
-      o = apply_diag<C>(a.diag, a.g, (int)b, (int)l, self);
+    if constexpr (CLOVER) {
+      o = diag44<C>(a.diag, b, l, psi);
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) o.s[s][c] = C(a.mass4) * self.s[s][c];
+        for (int c = 0; c < 3; ++c) o.s[s][c] = C(a.mass4) * psi.s[s][c];
     }
-    const C tau = C(a.tau[k0 + r]);
-    P* out = a.out + (size_t)(k0 + r) * a.fstride;
+    const C tau = C(a.tau[k]);
+    P* out = a.out + (size_t)k * a.fstride;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        cpx<C> v = o.s[s][c] - C(0.5) * acc[r].s[s][c];
-        if (MODE == 0) v = (s < 2) ? v - tau * self.s[s][c] : v + tau * self.s[s][c];
-        else v = (s < 2) ? v - tau * self.s[s][c] : -v - tau * self.s[s][c];
-        const uint32_t o = ((b * 12u + (uint32_t)(3 * s + c)) << 8) + l;
-        if (a.nt_out) sto_nt(out, o, vc(v, (P*)nullptr));
-        else sto(out, o, vc(v, (P*)nullptr));
+        cpx<C> v = o.s[s][c] - C(0.5) * acc.s[s][c];
+        if (MODE == 0) v = (s < 2) ? v - tau * psi.s[s][c] : v + tau * psi.s[s][c];
+        else v = (s < 2) ? v - tau * psi.s[s][c] : -v - tau * psi.s[s][c];
+        o.s[s][c] = v;
       }
-  }
+    if (a.nt_out) {
+#pragma unroll
+      for (int i = 0; i < 12; ++i) sto_nt(out, ((b * 12u + (uint32_t)i) << 8) + l, vc(o.s[i / 3][i % 3], (P*)nullptr));
+    } else {
+#pragma unroll
+      for (int i = 0; i < 12; ++i) sto(out, ((b * 12u + (uint32_t)i) << 8) + l, vc(o.s[i / 3][i % 3], (P*)nullptr));
+    }
+    if (TWO && k + 1 < kend) __syncthreads();  // the last direction's reads are done
   }
 }
 
-template <typename S, bool CLOVER, int MODE, int R, int W, bool LOOP = false, typename SI>
-void launch44(const DsArgs<S, SI>& a, int nb, hipStream_t s) {
-  const unsigned ng = LOOP ? 1u : (unsigned)((a.nrhs + R - 1) / R);
-  hipLaunchKernelGGL((k_dslash44<S, CLOVER, MODE, R, W, LOOP, SI>), dim3((unsigned)nb * ng), dim3(256), 0, s, a);
+// ---- 4^4 blocks, few of them: a work-group is a quarter of a block (64 sites), wave w
+// takes the two hops of direction w, so that a site's 8 hops are one round of loads instead
+// of a chain of them, and there are four times as many work-groups.
+template <typename C, int MU, typename PI, typename P>
+__device__ __forceinline__ void s44_pair(Spinor<C>& acc, const PI* in, const P* U, const int* nbr, uint32_t b,
+                                         uint32_t l) {
+  constexpr int SH = kL44Sh[MU];
+  const uint32_t lc = (l >> SH) & 3u;
+  const uint32_t bf = lc == 3u ? (uint32_t)nbr[b * 8 + 2 * MU] : b, bb = lc == 0u ? (uint32_t)nbr[b * 8 + 2 * MU + 1] : b;
+  const uint32_t lf = lc == 3u ? l - (3u << SH) : l + (1u << SH), lb = lc == 0u ? l + (3u << SH) : l - (1u << SH);
+  const Spinor<C> pf = ld_spinor44<C>(in, bf, lf), pb = ld_spinor44<C>(in, bb, lb);
+  const Link<C> uf = ld_link44<C>(U, b, MU, l), ub = ld_link44<C>(U, bb, MU, lb);
+  accum_recon(acc, umul(uf, project(pf, MU, true)), MU, true);
+  accum_recon(acc, udagmul(ub, project(pb, MU, false)), MU, false);
+}
+
+template <typename S, bool CLOVER, int MODE, typename SI>
+__global__ __launch_bounds__(256) void k_dslash44s(DsArgs<S, SI> a) {
+  using C = typename PT<S>::real;
+  using P = typename PT<S>::stor;
+  __shared__ cpx<C> part[4][12][64];
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const uint32_t l = ((blockIdx.x & 3u) << 6) | lane, i = blockIdx.x >> 2;
+  const uint32_t b = i / (uint32_t)a.nrhs, k = i - b * (uint32_t)a.nrhs;
+  const typename PT<SI>::stor* in = a.in + (size_t)k * a.fstride;
+  // waves 0 and 1 finish one chirality each; their site's terms arrive with the neighbours
+  cpx<C> v[6], dg[18];
+  if (wave < 2) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const auto t = cv(ldo(in, ((b * 12u + 6u * wave + (uint32_t)c) << 8) + l));
+      v[c] = cpx<C>{C(t.re), C(t.im)};
+    }
+    if (CLOVER)
+#pragma unroll
+      for (int c = 0; c < 18; ++c) {
+        const auto t = cv(ldo(a.diag, ((b * 36u + 18u * wave + (uint32_t)c) << 8) + l));
+        dg[c] = cpx<C>{C(t.re), C(t.im)};
+      }
+  }
+  Spinor<C> acc;
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
+  if (wave == 0) s44_pair<C, 0>(acc, in, a.U, a.g.nbr, b, l);
+  else if (wave == 1) s44_pair<C, 1>(acc, in, a.U, a.g.nbr, b, l);
+  else if (wave == 2) s44_pair<C, 2>(acc, in, a.U, a.g.nbr, b, l);
+  else s44_pair<C, 3>(acc, in, a.U, a.g.nbr, b, l);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) part[wave][c][lane] = acc.s[c / 3][c % 3];
+  __syncthreads();
+  if (wave >= 2) return;
+  cpx<C> w[6];
+  if (CLOVER) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      w[2 * q] = dg[q].re * v[2 * q];
+      w[2 * q + 1] = dg[q].im * v[2 * q + 1];
+    }
+    int q = 3;
+#pragma unroll
+    for (int r = 1; r < 6; ++r)
+#pragma unroll
+      for (int j = 0; j < r; ++j) {
+        w[r] = w[r] + dg[q] * v[j];
+        w[j] = w[j] + cmul_conj(dg[q], v[r]);
+        ++q;
+      }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) w[c] = C(a.mass4) * v[c];
+  }
+  const C tau = C(a.tau[k]);
+  P* out = a.out + (size_t)k * a.fstride;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const uint32_t at = 6u * wave + (uint32_t)c;
+    const cpx<C> hops = ((part[0][at][lane] + part[1][at][lane]) + part[2][at][lane]) + part[3][at][lane];
+    cpx<C> r = w[c] - C(0.5) * hops;
+    if (wave == 0) r = r - tau * v[c];
+    else if (MODE == 0) r = r + tau * v[c];
+    else r = -r - tau * v[c];
+    sto(out, ((b * 12u + at) << 8) + l, vc(r, (P*)nullptr));
+  }
+}
+
+template <typename S, bool CLOVER, int MODE, bool HOLD, typename SI>
+void launch44l(DsArgs<S, SI> a, int nb, int per, int nt, hipStream_t s) {
+  a.per = per;
+  a.ngrp = (a.nrhs + per - 1) / per;
+  a.nt_out = nt;
+  hipLaunchKernelGGL((k_dslash44l<S, CLOVER, MODE, SI, HOLD>), dim3((unsigned)(nb * a.ngrp)), dim3(256), 0, s, a);
 }
 
 template <typename S, bool CLOVER, int MODE, typename SI = S>
@@ -267,33 +446,42 @@ void launch_t(const qmg_ctx* c, void* out, const void* in, const double* tau, in
   a.nrhs = nrhs;
   a.remap = c->tune.dslash_xcd_remap;
   a.tord = c->d_tord;
-  a.tb = c->tile_blocks;
+  a.per = a.ngrp = 1;
   a.nt_out = 0;
   a.g = c->g;
   for (int i = 0; i < QMG_MAXRHS; ++i) a.tau[i] = i < nrhs ? tau[i] : 0.0;
-  const bool b44 = c->g.block[0] == 4 && c->g.block[1] == 4 && c->g.block[2] == 4 && c->g.block[3] == 4;
   const int var = c->tune.force_variant >= 0 ? c->tune.force_variant : c->tune.dslash[p][nrhs == 1 ? 0 : 1];
-  if (b44 && var > 0 && var < kNumDsVariants) {
-    switch (var) {
-      case 1: launch44<S, CLOVER, MODE, 1, 0>(a, c->g.nb, s); break;
-      case 2: launch44<S, CLOVER, MODE, 1, 2>(a, c->g.nb, s); break;
-      case 3: launch44<S, CLOVER, MODE, 1, 3>(a, c->g.nb, s); break;
-      case 4: launch44<S, CLOVER, MODE, 1, 4>(a, c->g.nb, s); break;
-      case 5: launch44<S, CLOVER, MODE, 2, 0>(a, c->g.nb, s); break;
-      case 6: launch44<S, CLOVER, MODE, 2, 2>(a, c->g.nb, s); break;
-      case 7: launch44<S, CLOVER, MODE, 4, 0>(a, c->g.nb, s); break;
-      case 8: launch44<S, CLOVER, MODE, 1, 2, true>(a, c->g.nb, s); break;
-      case 9: launch44<S, CLOVER, MODE, 2, 0, true>(a, c->g.nb, s); break;
-      case 10: launch44<S, CLOVER, MODE, 2, 2, true>(a, c->g.nb, s); break;
-      default: {
-        // variant 1 with the output streamed past the caches, which then keep the
-        // neighbour spinors, links and clover for longer
-        DsArgs<S, SI> an = a;
-        an.nt_out = 1;
-        launch44<S, CLOVER, MODE, 1, 0>(an, c->g.nb, s);
-        break;
+  if (fits44(c, p) && var > 0) {
+    // few blocks: the chain of loads of one thread per site is what a launch takes, so
+    // four (1 rhs, FP64: 8^4 11.3 -> 5.1 us, 16x16x8x8 12.3 -> 6.7; at 16^4 30 against 22;
+    // 8^4 with 16 rhs, FP32: 12.4 -> 10.7, FP64: 20 against 17)
+    constexpr int kFew = std::is_same<S, double>::value ? 128 : 256;
+    if ((int64_t)c->g.nb * nrhs <= kFew) {
+      hipLaunchKernelGGL((k_dslash44s<S, CLOVER, MODE, SI>), dim3(4u * c->g.nb * nrhs), dim3(256), 0, s, a);
+      return;
+    }
+    // an output that half fills the 256 MB Infinity Cache goes past it, and leaves it to the
+    // inputs (64x32^3, FP64: 1 rhs 0.705 -> 0.670 ms, 16 rhs 6.55 -> 6.22); a smaller one
+    // may still be there when it is read next
+    const int nt = (size_t)nrhs * field_elems(c) * cbytes(p) > ((size_t)128 << 20);
+    // FP32: links held over several right-hand sides (64x32^3, 16 rhs 3.82 -> 3.21 ms; BF16
+    // 2.25 against 2.34; FP64 has no registers for them), as few groups of them as fill the
+    // chip: the split with the fewest passes of (links + right-hand sides) over the 512
+    // work-groups that run at a time
+    if constexpr (std::is_same<S, float>::value) {
+      if (nrhs > 1 || c->g.nb > 512) {  // 1 rhs at 16^4: 14.6 us against 14.2
+        int per = 1;
+        int64_t cost = -1;
+        for (int g = 1; g <= nrhs; ++g) {
+          const int pg = (nrhs + g - 1) / g;
+          const int64_t t = (((int64_t)c->g.nb * g + 511) / 512) * (pg + 1);
+          if (cost < 0 || t < cost) { cost = t; per = pg; }
+        }
+        launch44l<S, CLOVER, MODE, true>(a, c->g.nb, per, nt, s);
+        return;
       }
     }
+    launch44l<S, CLOVER, MODE, false>(a, c->g.nb, 1, nt, s);
     return;
   }
   const int wg = 256;

@@ -16,15 +16,10 @@ inline size_t cbytes(int p) { return p == QMG_F64 ? 16 : (p == QMG_F32 ? 8 : 4);
 // coarse vectors are double for F64 and float otherwise
 inline int coarse_prec(int p) { return p == QMG_F64 ? QMG_F64 : QMG_F32; }
 
-// Stencil launch variants for 4^4 blocks: R right-hand sides per thread and a
-// waves-per-SIMD occupancy target W (0: compiler's choice).  Variant 0 is the
-// generic kernel (any block shape).
-struct DsVariant { int R, W; };
-// variants 8..10 walk all rhs groups of a block inside one work-group
-// variant 11 is variant 1 writing its output with non-temporal stores
-constexpr DsVariant kDsVariants[] = {{0, 0}, {1, 0}, {1, 2}, {1, 3}, {1, 4}, {2, 0}, {2, 2}, {4, 0},
-                                     {1, 2}, {2, 0}, {2, 2}, {1, 0}};
-constexpr int kNumDsVariants = 12;
+// Stencil variants: 0 the generic kernel (any block shape), 1 the 4^4-block kernels, chosen
+// among by batch and lattice size.  Tuning files may hold numbers up to 11: 4^4-block
+// kernels all.
+constexpr int kNumDsVariants = 12, kNumDsTuned = 2;
 // tiles of blocks (extent per direction, clamped to a divisor of the block grid)
 constexpr int kTileShapes[][4] = {{1, 1, 1, 1}, {2, 2, 2, 2}, {2, 2, 2, 4}, {2, 2, 4, 4},
                                   {1, 2, 4, 8}, {2, 2, 4, 8}, {1, 1, 2, 8}, {1, 2, 2, 4}};
@@ -39,8 +34,7 @@ struct Tune {
   int coarse_mfma = 1;                           // MFMA coarse apply for many right-hand sides
   int transfer_mr = 1;                           // restrict / prolong kernels sharing P loads across rhs
   int restrict_mfma_min_rhs = 4;                 // restriction on MFMA from this many rhs (1000: never)
-  int ds_order = 0;  // stencil work order: 0 blocks in lexicographic order, each with its rhs groups back to
-                     // back; t > 0 tiles of kTileShapes[t] blocks, each tile's rhs groups back to back
+  int ds_order = 0;  // stencil work order: 0 blocks in lexicographic order, t > 0 tiles of kTileShapes[t] blocks
   int coarse_mfma_min_rhs = 4;                   // smallest batch that takes the MFMA path
   bool tuned = false;
 };
@@ -68,8 +62,7 @@ struct qmg_ctx {
   int* d_nbr = nullptr;
   int* d_bcoord = nullptr;
   int* d_lexord = nullptr;
-  int* d_tord = nullptr;       // block ids in stencil work order (tiles of tile_blocks blocks)
-  int tile_blocks = 1;
+  int* d_tord = nullptr;       // block ids in stencil work order (tiles of blocks)
   std::vector<int> h_nbr, h_bcoord;
   std::vector<int64_t> lex_of_block;
   bool b44 = false;            // 4^4 blocks
@@ -97,6 +90,9 @@ struct qmg_ctx {
   hipEvent_t scratch_ev = nullptr;                // end of the last call that used the scratch of ws_try
   double* noalloc_scratch = nullptr;              // device address of this device's no-allocation scratch
 };
+
+// the 4^4-block kernels address the links (their largest array) with 32-bit byte offsets
+inline bool fits44(const qmg_ctx* c, int p) { return c->b44 && (uint64_t)c->g.nb * 36 * 256 * cbytes(p) <= (1ull << 32); }
 
 size_t field_elems(const qmg_ctx* c);   // complex elements in one fine field
 size_t coarse_elems(const qmg_ctx* c);  // complex elements in one coarse vector

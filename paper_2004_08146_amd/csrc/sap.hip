@@ -534,7 +534,7 @@ void launch_s(const qmg_ctx* c, int p, void* x, const void* f, const double* tau
   const int bs = 1 << c->g.bs_log;
   size_t lds = sizeof(cpx<R>) * 12 * bs + sizeof(R) * 3 * std::max(bs, 8);
   if constexpr (!std::is_same<S, double>::value) {
-    if (c->b44 && c->tune.sap_variant >= 1) {
+    if (fits44(c, p) && c->tune.sap_variant >= 1) {
       dim3 grid((unsigned)a.nblk);
       if (qf) {
         if (c->clover) hipLaunchKernelGGL((k_sap44<S, true, 2, true>), grid, dim3(512), 0, s, a);
@@ -572,7 +572,7 @@ hipError_t launch_sap(qmg_ctx* c, int p, void* x, const void* f, const double* t
   // every size measured (1.4-1.7 times, see there).  The kernels here that gather them
   // serve the other block shapes, and 4^4 blocks where that field may not be allocated
   // (a caller's stream capture, memory full) or a tuning file names them.
-  if (c->tune.sap_variant == 2 && c->b44 && nsweep > 0 && n_mr > 0) {
+  if (c->tune.sap_variant == 2 && fits44(c, p) && nsweep > 0 && n_mr > 0) {
     bool done = false;
     const hipError_t e = launch_sap44(c, p, x, f, tau, nrhs, nsweep, n_mr, s, qform, &done);
     if (e != hipSuccess || done) return e;

@@ -1,9 +1,8 @@
 // Launch-variant autotuner.
 //
 // For the context's lattice and block shape it times every stencil variant
-// (generic kernel; 4^4-block kernels with 1, 2 or 4 right-hand sides per
-// thread and occupancy targets) in FP64 / FP32 / BF16 for one and for sixteen
-// right-hand sides, and keeps the fastest per (precision, batch class).  The
+// (generic kernel, 4^4-block kernels) in FP64 / FP32 / BF16 for one and for
+// sixteen right-hand sides, and keeps the faster per (precision, batch class).  The
 // choice is cached in a JSON file keyed by GPU architecture, lattice, block
 // and clover flag; an existing entry is reused without timing (this is also
 // how a caller pins a variant).
@@ -93,7 +92,6 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
     c->tune.tuned = true;
     return QMG_OK;
   }
-  const bool b44 = c->g.block[0] == 4 && c->g.block[1] == 4 && c->g.block[2] == 4 && c->g.block[3] == 4;
   hipStream_t s = nullptr;
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
@@ -122,8 +120,8 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
         double best_ms = 1e30;
         int best = c->tune.dslash[p][cls];
         std::ostringstream times;
-        for (int v = 0; v < kNumDsVariants; ++v) {
-          if (v > 0 && !b44) break;
+        for (int v = 0; v < kNumDsTuned; ++v) {
+          if (v > 0 && !c->b44) break;
           c->tune.force_variant = v;
           hipError_t e = launch_dslash(c, p, out, in, tau.data(), n, 1, s);
           if (e == hipSuccess) e = hipEventRecord(e0, s);
@@ -163,7 +161,7 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
   }
   // work order of the stencil (tiles of blocks) under the chosen mapping and
   // variants: the sum over FP64 / FP32 with 1 and 16 rhs and the FGMRES product decides
-  if (st == QMG_OK && b44) {
+  if (st == QMG_OK && c->b44) {
     const size_t bytes = field_elems(c) * cbytes(QMG_F64) * 16;
     void* in = ws_get(c, "tune_in", bytes);
     void* out = ws_get(c, "tune_out", bytes);
@@ -205,7 +203,7 @@ qmg_status tune_run(qmg_ctx* c, const char* path) {
   }
   // SAP kernel choice (FP32 arithmetic paths), the three sweeps of a V-cycle on 16 rhs
   const int sap_default = c->tune.sap_variant;
-  for (int p = 1; p < 3 && st == QMG_OK && c->sap_ok && b44; ++p) {
+  for (int p = 1; p < 3 && st == QMG_OK && c->sap_ok && c->b44; ++p) {
     const int n = 16;
     const size_t bytes = field_elems(c) * cbytes(p) * n;
     void* x = ws_get(c, "tune_in", bytes);

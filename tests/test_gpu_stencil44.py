@@ -1,0 +1,54 @@
+"""Stencil kernels for 4^4 blocks: every way the launch picks between them."""
+import pytest
+
+from gpu_common import case, dev, host, need_gpu
+from helpers import oracle_at_sites, rel_err, sample_sites
+from oracle import clover as oclover
+from oracle import dirac
+from synth import random_links, random_spinors, seed_for
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+# 16 blocks: few (one thread per site and direction) up to 8 rhs in FP64, 16 in FP32 and
+# BF16; 32 blocks and more right-hand sides: a block per work-group, links held in FP32 and
+# split over groups; tolerances of the FP64, FP32 and BF16 stencil
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 8), 1), ((8, 8, 8, 8), 9), ((8, 8, 8, 8), 17), ((4, 8, 16, 16), 17),
+                                       ((4, 4, 4, 4), 3)])
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-13), ("f32", 1e-6), ("bf16", 3e-2)])
+@pytest.mark.parametrize("csw", [0.0, 1.0])
+def test_stencil_selection(dims, nrhs, prec, tol, csw):
+    case("stencil44 %s nrhs %d %s csw %g" % (dims, nrhs, prec, csw))
+    qmg = need_gpu()
+    U = random_links(dims, 0.5, seed_for(2, "U"))
+    lat = qmg.Lattice(dims, (4, 4, 4, 4))
+    lat.set_gauge(dev(U), -0.8, csw)
+    C = oclover.clover_term(U, csw) if csw else None
+    fin = lat.pack(dev(random_spinors(dims, nrhs, seed_for(2, "b"))), prec)
+    pin = host(lat.unpack(fin, nrhs, prec))
+    taus = [0.03 * (k + 1) for k in range(nrhs)]
+    q = host(lat.unpack(lat.apply_Q_shifted(lat.field(nrhs, prec), fin, taus, nrhs, prec), nrhs, prec))
+    a = host(lat.unpack(lat.apply_A(lat.field(nrhs, prec), fin, taus, nrhs, prec), nrhs, prec))
+    for k in sorted({0, nrhs // 2, nrhs - 1}):
+        assert rel_err(q[k], dirac.apply_Q_shifted(U, pin[k], -0.8, taus[k], C)) < tol
+        assert rel_err(a[k], dirac.apply_A(U, pin[k], -0.8, taus[k], C)) < tol
+
+
+# 512 and 1024 blocks: one right-hand side without and with held links, outputs past 128 MB
+@pytest.mark.parametrize("dims,nrhs,prec,tol", [((16, 16, 16, 32), 1, "f32", 1e-6), ((32, 16, 16, 32), 1, "f32", 1e-6),
+                                                ((16, 16, 16, 32), 13, "f32", 1e-6), ((16, 16, 16, 32), 6, "f64", 1e-13)])
+def test_stencil_selection_sampled(dims, nrhs, prec, tol):
+    case("stencil44 sampled %s nrhs %d %s" % (dims, nrhs, prec))
+    qmg = need_gpu()
+    U = random_links(dims, 0.5, seed_for(2, "U"))
+    lat = qmg.Lattice(dims, (4, 4, 4, 4))
+    lat.set_gauge(dev(U), -0.8, 1.0)
+    fin = lat.pack(dev(random_spinors(dims, nrhs, seed_for(2, "b"))), prec)
+    pin = lat.unpack(fin, nrhs, prec)
+    taus = [0.03 * (k + 1) for k in range(nrhs)]
+    q = lat.unpack(lat.apply_Q_shifted(lat.field(nrhs, prec), fin, taus, nrhs, prec), nrhs, prec)
+    sites = sample_sites(dims, 16, 4)
+    for k in sorted({0, nrhs - 1}):
+        ref = oracle_at_sites(U, host(pin[k]), -0.8, 1.0, sites, taus[k])
+        assert rel_err([host(q[k][x]) for x in sites], ref) < tol
