@@ -23,39 +23,44 @@ struct TauArr {
   int qform;  // 1: Gamma5^c (D_c - tau Gamma5^c) = Gamma5^c D_c - tau, the Galerkin P^H (Q - tau) P
 };
 
+// Few right-hand sides: one work-group per coarse site, wave d takes stencil entry d (the
+// nine are summed through LDS), lane i row i.  One wave doing the nine in turn left a
+// launch waiting for its loads: 41 us for 256 sites (ntv 24, FP64, 1 rhs), now 24, bound by
+// the row-wise reads of the four backward blocks.
 template <typename S, typename C, int T>
-__global__ __launch_bounds__(64) void k_coarse_apply(const int* nbr, int nb, typename PT<C>::stor* out,
-                                                     const typename PT<S>::stor* DcT, const typename PT<C>::stor* in,
-                                                     int nc, int nrhs, TauArr tau) {
+__global__ __launch_bounds__(576) void k_coarse_apply(const int* nbr, int nb, typename PT<C>::stor* out,
+                                                      const typename PT<S>::stor* DcT, const typename PT<C>::stor* in,
+                                                      int nc, int nrhs, TauArr tau) {
   using R = typename PT<C>::real;
   __shared__ cpx<R> xin[9][T][64];
-  const int b = blockIdx.x, k0 = blockIdx.y * T, tid = threadIdx.x;
-  for (int idx = tid; idx < 9 * T * nc; idx += blockDim.x) {
-    const int d = idx / (T * nc), t = (idx / nc) % T, j = idx % nc;
-    const int nbk = d == 0 ? b : nbr[b * 8 + d - 1];
+  const int b = blockIdx.x, k0 = blockIdx.y * T;
+  const int d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = threadIdx.x & 63;
+  const int nbk = d == 0 ? b : nbr[b * 8 + d - 1];
+  cpx<R> acc[T], self[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
     const int k = k0 + t;
-    xin[d][t][j] = k < nrhs ? ldcv<R>(in, ((int64_t)k * nb + nbk) * nc + j) : czero<R>();
+    self[t] = i < nc && k < nrhs ? ldcv<R>(in, ((int64_t)k * nb + nbk) * nc + i) : czero<R>();
+    xin[d][t][i] = self[t];
+    acc[t] = czero<R>();
   }
   __syncthreads();
-  const int i = tid;
-  if (i >= nc) return;
-  cpx<R> acc[T];
-#pragma unroll
-  for (int t = 0; t < T; ++t) acc[t] = czero<R>();
   const R g5 = i < nc / 2 ? R(1) : R(-1);
-  for (int d = 0; d < 9; ++d) {
+  if (i < nc) {
     if (d == 0 || (d & 1)) {
       // self (e = 0) or forward block e = 1 + mu of this site: row j of the transposed block
-      const auto* Dd = DcT + ((int64_t)b * 5 + (d + 1) / 2) * nc * nc;
+      const auto* Dd = DcT + ((int64_t)b * 5 + (d + 1) / 2) * nc * nc + i;
+#pragma unroll 8
       for (int j = 0; j < nc; ++j) {
-        const cpx<R> a = ldcv<R>(Dd, (int64_t)j * nc + i);
+        const cpx<R> a = ldcv<R>(Dd, (int64_t)j * nc);
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[t] = acc[t] + a * xin[d][t][j];
       }
     } else {
       // backward block: D_c[b][X - mu]_{ij} = g_i g_j conj(F_{ji}), F the forward block of
       // the site at X - mu, whose transposed storage holds F_{ji} at i * nc + j
-      const auto* Fd = DcT + ((int64_t)nbr[b * 8 + d - 1] * 5 + d / 2) * nc * nc + (int64_t)i * nc;
+      const auto* Fd = DcT + ((int64_t)nbk * 5 + d / 2) * nc * nc + (int64_t)i * nc;
+#pragma unroll 8
       for (int j = 0; j < nc; ++j) {
         const cpx<R> f = ldcv<R>(Fd, j);
         const R gg = j < nc / 2 ? g5 : -g5;
@@ -65,13 +70,20 @@ __global__ __launch_bounds__(64) void k_coarse_apply(const int* nbr, int nb, typ
       }
     }
   }
+  // each wave has read its own row of xin only
+#pragma unroll
+  for (int t = 0; t < T; ++t) xin[d][t][i] = acc[t];
+  __syncthreads();
+  if (d > 0 || i >= nc) return;
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int k = k0 + t;
-    if (k < nrhs) {
-      const cpx<R> v = acc[t] - (R(tau.t[k]) * g5) * xin[0][t][i];
-      stcv(out, ((int64_t)k * nb + b) * nc + i, tau.qform ? g5 * v : v);
-    }
+    if (k >= nrhs) break;
+    cpx<R> v = xin[0][t][i];
+#pragma unroll
+    for (int q = 1; q < 9; ++q) v = v + xin[q][t][i];
+    v = v - (R(tau.t[k]) * g5) * self[t];
+    stcv(out, ((int64_t)k * nb + b) * nc + i, tau.qform ? g5 * v : v);
   }
 }
 
@@ -96,7 +108,7 @@ template <> __device__ __forceinline__ int mrow<float>(int l, int r) { return 4 
 template <> __device__ __forceinline__ int mrow<double>(int l, int r) { return 4 * r + (l >> 4); }
 
 template <typename S, typename C, int NT>
-__global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, int nb, typename PT<C>::stor* out,
+__global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, const int* ord, int nb, typename PT<C>::stor* out,
                                                          const typename PT<S>::stor* DcT, const typename PT<C>::stor* in,
                                                          int nrhs, TauArr tau) {
   using R = typename PT<C>::real;
@@ -105,7 +117,11 @@ __global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, int nb,
   __shared__ cpx<R> Bs[NC][16];
   __shared__ cpx<R> Bself[NC][16];
   // one wave per 16-row tile t of the output; the waves share the staged inputs
-  const int b = blockIdx.x, n0 = blockIdx.y * 16, tid = threadIdx.x;
+  // each XCD walks a contiguous share of the sites in lexicographic order, so that a forward
+  // block is still in its L2 when the neighbour reads it as a backward block (in colour order
+  // that neighbour ran half a launch later: 32^4, FP32, 8 rhs 153 -> 140 us)
+  const int L = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  const int b = ord ? ord[L] : L, n0 = blockIdx.y * 16, tid = threadIdx.x;
   const int t = tid >> 6, l = tid & 63;
   const int ln = l & 15, lk = l >> 4;
   AT acc_re = AT{0, 0, 0, 0}, acc_im = AT{0, 0, 0, 0};
@@ -177,6 +193,7 @@ __global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, int nb,
 // (storage precision S) and the neighbour table
 struct CLevel {
   const int* nbr;
+  const int* ord;  // site ids in lexicographic order (null: they are)
   int nb, ntv;
   const void* D;
 };
@@ -190,10 +207,10 @@ void capply_mfma(const CLevel& lv, int p, void* out, const void* in, const TauAr
   auto go = [&](auto ntc) {
     constexpr int NT = decltype(ntc)::value;
     if (p == QMG_F64)
-      hipLaunchKernelGGL((k_coarse_mfma<S, double, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.nb, (double2*)out,
+      hipLaunchKernelGGL((k_coarse_mfma<S, double, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.ord, lv.nb, (double2*)out,
                          (const P*)lv.D, (const double2*)in, nrhs, tau);
     else
-      hipLaunchKernelGGL((k_coarse_mfma<S, float, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.nb, (float2*)out,
+      hipLaunchKernelGGL((k_coarse_mfma<S, float, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.ord, lv.nb, (float2*)out,
                          (const P*)lv.D, (const float2*)in, nrhs, tau);
   };
   if (nt == 3) go(std::integral_constant<int, 3>{});
@@ -207,10 +224,10 @@ void capply_t(const CLevel& lv, int p, void* out, const void* in, const TauArr& 
   const int nc = 2 * lv.ntv;
   dim3 grid(lv.nb, (nrhs + T - 1) / T);
   if (p == QMG_F64)
-    hipLaunchKernelGGL((k_coarse_apply<S, double, T>), grid, dim3(64), 0, s, lv.nbr, lv.nb, (double2*)out,
+    hipLaunchKernelGGL((k_coarse_apply<S, double, T>), grid, dim3(576), 0, s, lv.nbr, lv.nb, (double2*)out,
                        (const P*)lv.D, (const double2*)in, nc, nrhs, tau);
   else
-    hipLaunchKernelGGL((k_coarse_apply<S, float, T>), grid, dim3(64), 0, s, lv.nbr, lv.nb, (float2*)out,
+    hipLaunchKernelGGL((k_coarse_apply<S, float, T>), grid, dim3(576), 0, s, lv.nbr, lv.nb, (float2*)out,
                        (const P*)lv.D, (const float2*)in, nc, nrhs, tau);
 }
 
@@ -230,7 +247,7 @@ void capply_s(const qmg_ctx* c, const CLevel& lv, int p, void* out, const void* 
       return;
     }
   }
-  if (nrhs >= 4) capply_t<S, 4>(lv, p, out, in, t, nrhs, s);
+  if (nrhs >= 3) capply_t<S, 4>(lv, p, out, in, t, nrhs, s);
   else if (nrhs == 2) capply_t<S, 2>(lv, p, out, in, t, nrhs, s);
   else capply_t<S, 1>(lv, p, out, in, t, nrhs, s);
 }
@@ -240,7 +257,7 @@ void capply_s(const qmg_ctx* c, const CLevel& lv, int p, void* out, const void* 
 // tau: host array of nrhs shifts
 hipError_t launch_coarse_apply(const qmg_ctx* c, int p, void* out, const void* in, const double* dtau, int nrhs,
                                hipStream_t s, int qform) {
-  const CLevel lv{c->g.nbr, c->g.nb, c->ntv, c->Dc[p]};
+  const CLevel lv{c->g.nbr, c->g.lexord, c->g.nb, c->ntv, c->Dc[p]};
   if (p == QMG_F64) capply_s<double>(c, lv, p, out, in, dtau, nrhs, s, qform);
   else if (p == QMG_F32) capply_s<float>(c, lv, p, out, in, dtau, nrhs, s, qform);
   else capply_s<bf16_t>(c, lv, p, out, in, dtau, nrhs, s, qform);
@@ -251,7 +268,7 @@ hipError_t launch_coarse_apply(const qmg_ctx* c, int p, void* out, const void* i
 hipError_t launch_apply_l3(const qmg_ctx* c, int p, void* out, const void* in, const double* dtau, int nrhs,
                            hipStream_t s, int qform) {
   const int sp = p == QMG_F64 ? 0 : 1;
-  const CLevel lv{c->l3.nbr3, c->l3.n3, c->l3.ntv2, c->l3.D3[sp]};
+  const CLevel lv{c->l3.nbr3, nullptr, c->l3.n3, c->l3.ntv2, c->l3.D3[sp]};
   if (p == QMG_F64) capply_s<double>(c, lv, p, out, in, dtau, nrhs, s, qform);
   else capply_s<float>(c, lv, p, out, in, dtau, nrhs, s, qform);
   return hipGetLastError();

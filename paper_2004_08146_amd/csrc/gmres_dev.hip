@@ -16,6 +16,7 @@
 #include <string>
 
 #include "qmg_ctx.h"
+#include "reduce.h"
 
 namespace {
 
@@ -46,71 +47,112 @@ __global__ void k_gm_init(GmState st, const double* norms, double* a, int nrhs) 
   for (int i = 0; i <= m; ++i) st.sig[(int64_t)k * (m + 1) + i] = i == 0 ? 1.0 : 0.0;
 }
 
-// one classical Gram-Schmidt pass for w = A W_j, d_i = W_i^H w:
-// H[i][j] = sig_i sig_j d_i, coef_i = -sig_i^2 d_i (w -= (v_i^H w) v_i).
-// last: dots also holds ||w||^2 (at index J), and norms[2k] gets the squared
-// norm of the projected w, ||w||^2 - sum_i sig_i^2 |d_i|^2, in place of the
-// update pass
-__global__ void k_gm_coef(GmState st, const double* dots, double* coef, int j, int nrhs, int last,
-                          double* norms) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nrhs) return;
-  const int J = j + 1, m = st.m, ld = J + (last ? 1 : 0);
-  const double* sg = st.sig + (int64_t)k * (m + 1);
-  double proj = 0.0;
-  for (int i = 0; i < J; ++i) {
-    const cpx<double> d = ldz(dots, (int64_t)k * ld + i);
-    const int64_t hi = (int64_t)k * (m + 1) * m + (int64_t)i * m + j;
-    stz(st.H, hi, ldz(st.H, hi) + (sg[i] * sg[j]) * d);
-    stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * d);
-    proj += sg[i] * sg[i] * norm2(d);
+constexpr int kGmWG = 256;
+// sums of the nchunk partial results (pairs) of value j, in every thread's out[j], j < J
+__device__ void gm_sums(const double* partial, int J, int nchunk, double (*out)[2]) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int j = wave; j < J; j += kGmWG / 64) {
+    double re = 0.0, im = 0.0;
+    for (int c = lane; c < nchunk; c += 64) {
+      re += partial[((int64_t)j * nchunk + c) * 2];
+      im += partial[((int64_t)j * nchunk + c) * 2 + 1];
+    }
+    re = wave_sum63(re);
+    im = wave_sum63(im);
+    if (lane == 63) {
+      out[j][0] = re;
+      out[j][1] = im;
+    }
   }
-  if (last) {
-    norms[2 * k] = fmax(dots[2 * ((int64_t)k * ld + J)] - proj, 0.0);
-    norms[2 * k + 1] = 0.0;
-  }
+  __syncthreads();
 }
 
 // close column j: h_{j+1,j} = sig_j ||w_new|| (w_new = the projected A W_j,
-// stored as W_{j+1}, so sig_{j+1} = 1 / ||w_new||), rotate, update g
-__global__ void k_gm_col(GmState st, const double* norms, int j, int nrhs) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nrhs) return;
+// stored as W_{j+1}, so sig_{j+1} = 1 / ||w_new||), rotate, update g; one thread,
+// hc: the column's entries 0..j
+__device__ void gm_close(const GmState& st, int k, int j, double norm2w, double (*hc)[2]) {
   const int m = st.m;
   double* H = st.H + (int64_t)k * (m + 1) * m * 2;
   double* g = st.g + (int64_t)k * (m + 1) * 2;
   double* cs = st.cs + (int64_t)k * m;
   double* sn = st.sn + (int64_t)k * m * 2;
   double* sg = st.sig + (int64_t)k * (m + 1);
-  const double wn = sqrt(fmax(norms[2 * k], 0.0));
+  const double wn = sqrt(fmax(norm2w, 0.0));
   const double hn = sg[j] * wn;
   sg[j + 1] = wn > 0 ? 1.0 / wn : 0.0;
-  cpx<double> h[2];
+  cpx<double> cur = {hc[0][0], hc[0][1]};
   for (int i = 0; i < j; ++i) {
-    const cpx<double> hi = ldz(H, (int64_t)i * m + j), hi1 = ldz(H, (int64_t)(i + 1) * m + j);
+    const cpx<double> hi1 = {hc[i + 1][0], hc[i + 1][1]};
     const double c = cs[i];
     const cpx<double> s = ldz(sn, i);
-    stz(H, (int64_t)i * m + j, c * hi + s * hi1);
-    stz(H, (int64_t)(i + 1) * m + j, c * hi1 - conj(s) * hi);
+    stz(H, (int64_t)i * m + j, c * cur + s * hi1);
+    cur = c * hi1 - conj(s) * cur;
   }
-  h[0] = ldz(H, (int64_t)j * m + j);
-  h[1] = cpx<double>{hn, 0.0};
+  const cpx<double> h1 = {hn, 0.0};
   double c;
   cpx<double> s;
-  const double na = sqrt(norm2(h[0])), nb = hn;
+  const double na = sqrt(norm2(cur)), nb = hn;
   if (nb == 0.0) { c = 1.0; s = czero<double>(); }
   else if (na == 0.0) { c = 0.0; s = cpx<double>{1.0, 0.0}; }
   else {
     const double rho = sqrt(na * na + nb * nb);
     c = na / rho;
-    s = (1.0 / (na * rho)) * (h[0] * conj(h[1]));
+    s = (1.0 / (na * rho)) * (cur * conj(h1));
   }
   cs[j] = c;
   stz(sn, j, s);
-  stz(H, (int64_t)j * m + j, c * h[0] + s * h[1]);
+  stz(H, (int64_t)j * m + j, c * cur + s * h1);
   const cpx<double> gj = ldz(g, j);
   stz(g, j + 1, -(conj(s) * gj));
   stz(g, j, c * gj);
+}
+
+// One classical Gram-Schmidt pass for w = A W_j, d_i = W_i^H w summed here from the chunk
+// sums: H[i][j] = sig_i sig_j d_i, coef_i = -sig_i^2 d_i (w -= (v_i^H w) v_i).
+// last: the sums also hold ||w||^2 (at index J); the squared norm of the projected w,
+// ||w||^2 - sum_i sig_i^2 |d_i|^2, takes the place of the update pass and the column is
+// closed at once.  One work-group per right-hand side, which also closes the column where
+// five launches of a few waves did (16 of 32 us a step at 32^4, 8 rhs, now 11).
+// longcol: work-group k's column in memory, for more steps than fit in LDS (else null).
+__global__ __launch_bounds__(kGmWG) void k_gm_coef(GmState st, const double* partial, int nchunk, double* coef, int j,
+                                                   int last, double* longcol) {
+  extern __shared__ double gsh[];
+  const int k = blockIdx.x;
+  double(*d)[2] = reinterpret_cast<double(*)[2]>(longcol ? longcol + (int64_t)k * 2 * (st.m + 2) : gsh);
+  const int J = j + 1, m = st.m, ld = J + (last ? 1 : 0);
+  gm_sums(partial + (int64_t)k * ld * nchunk * 2, ld, nchunk, d);
+  const double* sg = st.sig + (int64_t)k * (m + 1);
+  for (int i = threadIdx.x; i < J; i += kGmWG) {
+    const cpx<double> di = {d[i][0], d[i][1]};
+    stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * di);
+    if (!last) stz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j, (sg[i] * sg[j]) * di);
+  }
+  if (last && threadIdx.x == 0) {
+    double proj = 0.0;
+    for (int i = 0; i < J; ++i) {
+      const double s2 = sg[i] * sg[i];
+      proj += s2 * (d[i][0] * d[i][0] + d[i][1] * d[i][1]);
+      d[i][0] *= sg[i] * sg[j];
+      d[i][1] *= sg[i] * sg[j];
+    }
+    gm_close(st, k, j, fmax(d[J][0] - proj, 0.0), d);
+  }
+}
+
+// closes column j from the chunk sums of ||w_new||^2
+__global__ __launch_bounds__(kGmWG) void k_gm_col(GmState st, const double* partial, int nchunk, int j,
+                                                  double* longcol) {
+  extern __shared__ double gsh[];
+  __shared__ double nrm[1][2];
+  const int k = blockIdx.x, m = st.m;
+  double(*hc)[2] = reinterpret_cast<double(*)[2]>(longcol ? longcol + (int64_t)k * 2 * (m + 2) : gsh);
+  for (int i = threadIdx.x; i <= j; i += kGmWG) {
+    const cpx<double> h = ldz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j);
+    hc[i][0] = h.re;
+    hc[i][1] = h.im;
+  }
+  gm_sums(partial + (int64_t)k * nchunk * 2, 1, nchunk, nrm);
+  if (threadIdx.x == 0) gm_close(st, k, j, nrm[0][0], hc);
 }
 
 // y = R^{-1} g (R: the rotated Hessenberg, kk columns) -> coef[k][0..kk)
@@ -161,7 +203,6 @@ static qmg_status gmres_device(qmg_ctx* c, const DevOp& op, void* y, const void*
   const bool flex = (bool)op.prec;
   void* V = ws_get(c, tag + "_V", bb * (m + 1));
   void* Z = flex ? ws_get(c, tag + "_Z", bb * m) : nullptr;
-  double* dots = (double*)ws_get(c, tag + "_dots", sizeof(double) * 2 * (m + 2) * nrhs);
   double* part = (double*)ws_get(c, tag + "_part", sizeof(double) * multidot_partial_doubles(n, m + 2, nrhs));
   double* coef = (double*)ws_get(c, tag + "_coef", sizeof(double) * 2 * (m + 1) * nrhs);
   double* a = (double*)ws_get(c, tag + "_a", sizeof(double) * 2 * nrhs);
@@ -174,11 +215,15 @@ static qmg_status gmres_device(qmg_ctx* c, const DevOp& op, void* y, const void*
   st.sn = (double*)ws_get(c, tag + "_sn", sizeof(double) * 2 * m * nrhs);
   st.beta = (double*)ws_get(c, tag + "_beta", sizeof(double) * nrhs);
   st.sig = (double*)ws_get(c, tag + "_sig", sizeof(double) * (m + 1) * nrhs);
-  if (!V || (flex && !Z) || !dots || !part || !coef || !a || !nrm || !st.H || !st.g || !st.cs || !st.sn ||
+  if (!V || (flex && !Z) || !part || !coef || !a || !nrm || !st.H || !st.g || !st.cs || !st.sn ||
       !st.beta || !st.sig)
     return set_err(c, QMG_E_NOMEM, "out of device memory (device GMRES)");
   const dim3 g1((nrhs + 63) / 64), b1(64);
   const int64_t vs = n * nrhs;
+  const int nchunk = dot_chunks(n);
+  const bool big = m > 2000;
+  double* longcol = big ? (double*)ws_get(c, tag + "_dots", sizeof(double) * 2 * (m + 2) * nrhs) : nullptr;
+  if (big && !longcol) return set_err(c, QMG_E_NOMEM, "out of device memory (device GMRES)");
   hipError_t e = launch_multidot(cp, nrm, r, 0, 0, r, n, n, nrhs, part, s, 1);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_gm_init, g1, b1, 0, s, st, nrm, a, nrhs);
@@ -196,12 +241,16 @@ static qmg_status gmres_device(qmg_ctx* c, const DevOp& op, void* y, const void*
     } else {
       e = op.apply(w, Vj);
     }
-    if (e == hipSuccess) e = launch_multidot(cp, dots, V, vs, j + 1, w, n, n, nrhs, part, s, last);
+    const size_t lds = longcol ? 0 : sizeof(double) * 2 * (j + 2);
+    if (e == hipSuccess) e = launch_dot_partials(cp, V, vs, j + 1, w, n, n, nrhs, part, s, last);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_gm_coef, g1, b1, 0, s, st, dots, coef, j, nrhs, last, nrm);
-      if (!last) e = launch_axpy_norm(cp, w, V, vs, j + 1, coef, n, n, nrhs, nrm, part, s);
+      hipLaunchKernelGGL(k_gm_coef, dim3(nrhs), dim3(kGmWG), lds, s, st, part, nchunk, coef, j, last, longcol);
+      if (!last) {
+        e = launch_axpy_partials(cp, w, V, vs, j + 1, coef, n, n, nrhs, part, s);
+        if (e == hipSuccess) hipLaunchKernelGGL(k_gm_col, dim3(nrhs), dim3(kGmWG), lds, s, st, part, nchunk, j, longcol);
+      }
+      if (e == hipSuccess) e = hipGetLastError();
     }
-    if (e == hipSuccess) hipLaunchKernelGGL(k_gm_col, g1, b1, 0, s, st, nrm, j, nrhs);
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_gm_solve, g1, b1, 0, s, st, coef, m, nrhs);

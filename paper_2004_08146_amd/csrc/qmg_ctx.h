@@ -163,6 +163,14 @@ qmg_status solver_setup_l3(qmg_ctx* c, void* W2, int ntv2, const int block2[4], 
 // dots[k*J + j] = <V_j,k , w_k> for j < J (V_j at base + j*vstride), FP64 results on device
 hipError_t launch_multidot(int p, double* dots, const void* V, int64_t vstride, int J, const void* w,
                            int64_t n, int64_t stride, int nrhs, double* partial, hipStream_t s, int with_self = 0);
+// the chunk sums only: partial[((k*(J + with_self) + j)*dot_chunks(n) + chunk)*2 ..]
+int dot_chunks(int64_t n);
+hipError_t launch_dot_partials(int p, const void* V, int64_t vstride, int J, const void* w, int64_t n, int64_t stride,
+                               int nrhs, double* partial, hipStream_t s, int with_self = 0);
+// the update and the chunk sums of its squared norm: partial[(k*dot_chunks(n) + chunk)*2 ..]
+hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
+                                int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy = nullptr,
+                                int copy_prec = QMG_F64);
 // w_k += sum_j coef[k*J + j] V_j,k and norms[2k] = ||w_k||^2 of the result; with copy
 // (p == QMG_F64 only) the result is also written there in copy_prec (FP32 or BF16),
 // bit for bit what launch_convert would write
