@@ -366,6 +366,7 @@ qmg_status qmg_destroy(qmg_ctx* c) {
     free_ptr(c->Dg[p]);
   }
   for (auto& kv : c->ws) hipFree(kv.second.first);
+  for (auto& kv : c->hbuf) hipHostFree(kv.second.first);
   if (c->d_nbr) hipFree(c->d_nbr);
   if (c->d_bcoord) hipFree(c->d_bcoord);
   if (c->d_lexord) hipFree(c->d_lexord);

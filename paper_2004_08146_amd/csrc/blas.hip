@@ -148,6 +148,52 @@ __global__ __launch_bounds__(256) void k_dot_stage2(double* dots, const double* 
   }
 }
 
+// As k_dot_stage2 for the projections of one Gram-Schmidt pass: dots as it, and for j < J
+// also the update's coefficients coef[k*J + j] = -sig_j^2 dots (basis v_j = sig_j W_j)
+__global__ __launch_bounds__(256) void k_project_stage2(double* dots, double* coef, const double* partial,
+                                                        const double* sig, int ldsig, int J, int JT, int nchunk) {
+  __shared__ double red[2 * 4];
+  const int j = blockIdx.x, k = blockIdx.y;
+  const double* p = partial + ((int64_t)k * JT + j) * nchunk * 2;
+  double acc[2] = {0.0, 0.0};
+  for (int c = threadIdx.x; c < nchunk; c += blockDim.x) {
+    acc[0] += p[2 * c];
+    acc[1] += p[2 * c + 1];
+  }
+  wg_sum<double, 2>(acc, red);
+  if (threadIdx.x == 0) {
+    dots[((int64_t)k * JT + j) * 2] = acc[0];
+    dots[((int64_t)k * JT + j) * 2 + 1] = acc[1];
+    if (j < J) {
+      const double s = sig[(int64_t)k * ldsig + j], s2 = -s * s;
+      coef[((int64_t)k * J + j) * 2] = s2 * acc[0];
+      coef[((int64_t)k * J + j) * 2 + 1] = s2 * acc[1];
+    }
+  }
+}
+
+// norms[2k] = ||w_k||^2 and the scale of w_k as basis vector `at`: sig = 1 / ||w_k||
+__global__ __launch_bounds__(256) void k_norm_stage2(double* norms, const double* partial, double* sig, int ldsig,
+                                                     int at, int nchunk) {
+  __shared__ double red[2 * 4];
+  const int k = blockIdx.x;
+  const double* p = partial + (int64_t)k * nchunk * 2;
+  double acc[2] = {0.0, 0.0};
+  for (int c = threadIdx.x; c < nchunk; c += blockDim.x) acc[0] += p[2 * c];
+  wg_sum<double, 2>(acc, red);
+  if (threadIdx.x == 0) {
+    norms[2 * k] = acc[0];
+    norms[2 * k + 1] = 0.0;
+    const double h = sqrt(fmax(acc[0], 0.0));
+    sig[(int64_t)k * ldsig + at] = h > 0.0 && isfinite(h) ? 1.0 / h : 0.0;
+  }
+}
+
+__global__ void k_sig_init(double* sig, int ldsig, int nrhs) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < ldsig * nrhs) sig[i] = i % ldsig == 0 ? 1.0 : 0.0;
+}
+
 template <typename S, typename SV = S>
 __global__ __launch_bounds__(256) void k_multiaxpy(typename PT<S>::stor* w, const typename PT<SV>::stor* V,
                                                    int64_t vstride, int J, const double* coef, int64_t n,
@@ -298,6 +344,30 @@ hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int 
   const hipError_t e = launch_axpy_partials(p, w, V, vstride, J, coef, n, stride, nrhs, partial, s, copy, copy_prec);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dot_stage2, dim3(1, nrhs), dim3(256), 0, s, norms, partial, 1, dot_chunks(n));
+  return hipGetLastError();
+}
+
+hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
+                          int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
+                          hipStream_t s, int with_self) {
+  const hipError_t e = launch_dot_partials(p, V, vstride, J, w, n, stride, nrhs, partial, s, with_self);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_project_stage2, dim3(J + with_self, nrhs), dim3(256), 0, s, dots, coef, partial, sig, ldsig, J,
+                     J + with_self, dot_chunks(n));
+  return hipGetLastError();
+}
+
+hipError_t launch_axpy_sig(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
+                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int at, double* partial,
+                           hipStream_t s, void* copy, int copy_prec) {
+  const hipError_t e = launch_axpy_partials(p, w, V, vstride, J, coef, n, stride, nrhs, partial, s, copy, copy_prec);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_norm_stage2, dim3(nrhs), dim3(256), 0, s, norms, partial, sig, ldsig, at, dot_chunks(n));
+  return hipGetLastError();
+}
+
+hipError_t launch_sig_init(double* sig, int ldsig, int nrhs, hipStream_t s) {
+  hipLaunchKernelGGL(k_sig_init, dim3((ldsig * nrhs + 255) / 256), dim3(256), 0, s, sig, ldsig, nrhs);
   return hipGetLastError();
 }
 

@@ -81,7 +81,7 @@ struct qmg_ctx {
   Level3 l3;
   // workspace
   std::map<std::string, std::pair<void*, size_t>> ws;
-  std::map<std::string, std::vector<double>> hbuf;  // host staging for small Krylov data
+  std::map<std::string, std::pair<double*, size_t>> hbuf;  // pinned host staging for small Krylov data
   std::string err;
   Tune tune;
   std::map<std::string, hipGraphExec_t> graphs;  // captured V-cycles by (buffers, shifts, parameters)
@@ -177,6 +177,17 @@ hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, 
 hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                             int64_t stride, int nrhs, double* norms, double* partial, hipStream_t s,
                             void* copy = nullptr, int copy_prec = QMG_F64);
+// One Gram-Schmidt pass on a basis v_j = sig_j W_j (sig: [nrhs][ldsig] on the device): the
+// projections dots (as launch_multidot) with the update's coefficients -sig_j^2 dots, and
+// the update with the squared norms of its results and their scales as basis vector `at`
+hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
+                          int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
+                          hipStream_t s, int with_self);
+hipError_t launch_axpy_sig(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
+                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int at, double* partial,
+                           hipStream_t s, void* copy = nullptr, int copy_prec = QMG_F64);
+// sig = (1, 0, 0, ...) for every right-hand side
+hipError_t launch_sig_init(double* sig, int ldsig, int nrhs, hipStream_t s);
 // w_k += sum_j coef[k*J + j] * V_j,k   (coef complex double on device)
 hipError_t launch_multiaxpy(int p, void* w, const void* V, int64_t vstride, int J, const double* coef,
                             int64_t n, int64_t stride, int nrhs, hipStream_t s);

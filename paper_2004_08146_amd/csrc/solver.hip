@@ -78,10 +78,19 @@ struct Lsq {
 // squared norm ratio below which a second Gram-Schmidt pass is made
 constexpr double kReorthRatio2 = 0.05 * 0.05;
 
+// pinned, so that copies neither stage through another buffer nor wait for it; nullptr on failure.
+// A buffer that has to grow is idle: every use of it ends with a synchronisation
 double* host_buf(qmg_ctx* c, const std::string& name, size_t ndouble) {
   auto& v = c->hbuf[name];
-  if (v.size() < ndouble) v.resize(ndouble);
-  return v.data();
+  if (v.second < ndouble) {
+    if (v.first) hipHostFree(v.first);
+    v = {nullptr, 0};
+    void* p = nullptr;
+    const size_t n = std::max<size_t>(2 * ndouble, 512);
+    if (hipHostMalloc(&p, n * sizeof(double), hipHostMallocDefault) != hipSuccess) return nullptr;
+    v = {(double*)p, n};
+  }
+  return v.first;
 }
 
 // batched vector space helper (n complex per vector, nrhs vectors per batch)
@@ -104,6 +113,7 @@ struct Space {
     hipError_t e = launch_multidot(p, d, V, vstr, J, w, n, n, nrhs, part, s);
     if (e != hipSuccess) return hip_err(c, e, "multidot");
     double* h = host_buf(c, "dots", 2 * J * nrhs);
+    if (!h) return set_err(c, QMG_E_NOMEM, "out of host memory (dots)");
     e = hipMemcpyAsync(h, d, sizeof(double) * 2 * J * nrhs, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_err(c, e, "dots D2H");
@@ -127,6 +137,7 @@ struct Space {
     double* d = (double*)ws_get(c, "sp_coef", sizeof(double) * 2 * J * nrhs);
     if (!d) return set_err(c, QMG_E_NOMEM, "out of device memory (coef)");
     double* h = host_buf(c, "coef", 2 * J * nrhs);
+    if (!h) return set_err(c, QMG_E_NOMEM, "out of host memory (coef)");
     for (int i = 0; i < J * nrhs; ++i) { h[2 * i] = coef[i].real(); h[2 * i + 1] = coef[i].imag(); }
     hipError_t e = hipMemcpyAsync(d, h, sizeof(double) * 2 * J * nrhs, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
@@ -140,6 +151,7 @@ struct Space {
     double* d = (double*)ws_get(c, "sp_scale", sizeof(double) * 2 * nrhs);
     if (!d) return set_err(c, QMG_E_NOMEM, "out of device memory (scale)");
     double* h = host_buf(c, "scale", 2 * nrhs);
+    if (!h) return set_err(c, QMG_E_NOMEM, "out of host memory (scale)");
     for (int k = 0; k < nrhs; ++k) { h[2 * k] = a[k].real(); h[2 * k + 1] = a[k].imag(); }
     hipError_t e = hipMemcpyAsync(d, h, sizeof(double) * 2 * nrhs, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_scale(p, y, x, d, n, n, nrhs, s, copy, copy_prec);
@@ -153,45 +165,40 @@ struct Space {
   // One pass leaves an orthogonality error of about eps ||w|| / ||w_new||
   // (<= 20 eps here); the true residual is recomputed after every restart
   // cycle anyway.  The new norm comes out of the update pass.
-  // sig (optional, [nrhs][j + 1]): the basis is stored unnormalised, v_i = sig_i W_i,
-  // so the projections use sig_i (W_i^H w) and the update subtracts sig_i^2 (W_i^H w) W_i.
+  // The basis is stored unnormalised, v_i = sig_i W_i, sig ([nrhs][j + 1]) here and in
+  // dsig ([nrhs][ldsig]) on the device: the projections use sig_i (W_i^H w) and the update
+  // subtracts sig_i^2 (W_i^H w) W_i.  The update's coefficients are formed on the device and
+  // projections and norm are read together, so a pass waits once.
   // copy (optional): the update pass also writes the new w there in copy_prec.
   qmg_status arnoldi(std::vector<std::vector<cd>>& h, void* V, int j, void* w,
-                     const std::vector<std::vector<double>>* sig = nullptr, void* copy = nullptr,
+                     const std::vector<std::vector<double>>& sig, double* dsig, int ldsig, void* copy = nullptr,
                      int copy_prec = QMG_F64) {
     const int J = j + 1;
     h.assign(nrhs, std::vector<cd>(j + 2, cd(0)));
-    double* d = (double*)ws_get(c, "sp_dots", sizeof(double) * 2 * (J + 1) * nrhs);
+    const size_t nd = 2 * (size_t)(J + 1) * nrhs, nres = nd + 2 * nrhs;  // projections, then norms
+    double* d = (double*)ws_get(c, "sp_dots", sizeof(double) * nres);
     double* part = (double*)ws_get(c, "sp_part", sizeof(double) * multidot_partial_doubles(n, J + 1, nrhs));
     double* dc = (double*)ws_get(c, "sp_coef", sizeof(double) * 2 * J * nrhs);
     if (!d || !part || !dc) return set_err(c, QMG_E_NOMEM, "out of device memory (Arnoldi)");
-    double* hd = host_buf(c, "dots", 2 * (J + 1) * nrhs);
-    double* hc = host_buf(c, "coef", 2 * J * nrhs);
+    double* hd = host_buf(c, "dots", nres);
+    if (!hd) return set_err(c, QMG_E_NOMEM, "out of host memory (Arnoldi)");
     std::vector<double> before(nrhs), after(nrhs);
     for (int pass = 0; pass < 2; ++pass) {
       const int self = pass == 0 ? 1 : 0;
-      hipError_t e = launch_multidot(p, d, V, vstride(), J, w, n, n, nrhs, part, s, self);
-      if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * 2 * (J + self) * nrhs, hipMemcpyDeviceToHost, s);
+      hipError_t e = launch_project(p, d, dc, dsig, ldsig, V, vstride(), J, w, n, n, nrhs, part, s, self);
+      if (e == hipSuccess)
+        e = launch_axpy_sig(p, w, V, vstride(), J, dc, n, n, nrhs, d + nd, dsig, ldsig, J, part, s, copy, copy_prec);
+      if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * nres, hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
-      if (e != hipSuccess) return hip_err(c, e, "Arnoldi dots");
+      if (e != hipSuccess) return hip_err(c, e, "Arnoldi step");
+      bool again = false;
       for (int k = 0; k < nrhs; ++k) {
         for (int i = 0; i < J; ++i) {
           const double* q = hd + 2 * ((size_t)k * (J + self) + i);
-          const double si = sig ? (*sig)[k][i] : 1.0;
-          h[k][i] += si * cd(q[0], q[1]);
-          hc[2 * ((size_t)k * J + i)] = -si * si * q[0];
-          hc[2 * ((size_t)k * J + i) + 1] = -si * si * q[1];
+          h[k][i] += sig[k][i] * cd(q[0], q[1]);
         }
         if (self) before[k] = hd[2 * ((size_t)k * (J + 1) + J)];
-      }
-      e = hipMemcpyAsync(dc, hc, sizeof(double) * 2 * J * nrhs, hipMemcpyHostToDevice, s);
-      if (e == hipSuccess) e = launch_axpy_norm(p, w, V, vstride(), J, dc, n, n, nrhs, d, part, s, copy, copy_prec);
-      if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * 2 * nrhs, hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = hipStreamSynchronize(s);
-      if (e != hipSuccess) return hip_err(c, e, "Arnoldi update");
-      bool again = false;
-      for (int k = 0; k < nrhs; ++k) {
-        after[k] = hd[2 * k];
+        after[k] = hd[nd + 2 * k];
         if (!std::isfinite(after[k]) || !std::isfinite(before[k]))
           return set_err(c, QMG_E_NUMERIC, "non-finite norm in Arnoldi step");
         if (after[k] < kReorthRatio2 * before[k]) again = true;
@@ -209,13 +216,14 @@ struct Space {
   // orthonormal. The subtraction loses about eps ||w||^2 / ||w_new||^2 in
   // relative accuracy, which only perturbs this cycle's last rotation.
   qmg_status arnoldi_last(std::vector<std::vector<cd>>& h, void* V, int j, void* w,
-                          const std::vector<std::vector<double>>* sig = nullptr) {
+                          const std::vector<std::vector<double>>& sig) {
     const int J = j + 1;
     h.assign(nrhs, std::vector<cd>(j + 2, cd(0)));
     double* d = (double*)ws_get(c, "sp_dots", sizeof(double) * 2 * (J + 1) * nrhs);
     double* part = (double*)ws_get(c, "sp_part", sizeof(double) * multidot_partial_doubles(n, J + 1, nrhs));
     if (!d || !part) return set_err(c, QMG_E_NOMEM, "out of device memory (Arnoldi)");
     double* hd = host_buf(c, "dots", 2 * (J + 1) * nrhs);
+    if (!hd) return set_err(c, QMG_E_NOMEM, "out of host memory (Arnoldi)");
     hipError_t e = launch_multidot(p, d, V, vstride(), J, w, n, n, nrhs, part, s, 1);
     if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * 2 * (J + 1) * nrhs, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -224,8 +232,7 @@ struct Space {
       double proj = 0.0;
       for (int i = 0; i < J; ++i) {
         const double* q = hd + 2 * ((size_t)k * (J + 1) + i);
-        const double si = sig ? (*sig)[k][i] : 1.0;
-        h[k][i] = si * cd(q[0], q[1]);
+        h[k][i] = sig[k][i] * cd(q[0], q[1]);
         proj += std::norm(h[k][i]);
       }
       const double ww = hd[2 * ((size_t)k * (J + 1) + J)];
@@ -245,8 +252,8 @@ qmg_status solver_coarse_gmres(qmg_ctx* c, int p, void* y, const void* r, const 
   Space sp{c, cp, (int64_t)coarse_elems(c), nrhs, s};
   if (iters < 1) iters = 1;
   void* V = ws_get(c, "cg_V", sp.bbytes() * (iters + 1));
-  void* w = ws_get(c, "cg_w", sp.bbytes());
-  if (!V || !w) return set_err(c, QMG_E_NOMEM, "out of device memory (coarse GMRES)");
+  double* dsig = (double*)ws_get(c, "cg_dsig", sizeof(double) * (iters + 1) * nrhs);
+  if (!V || !dsig) return set_err(c, QMG_E_NOMEM, "out of device memory (coarse GMRES)");
   std::vector<double> beta;
   qmg_status st = sp.norms(beta, r);
   if (st != QMG_OK) return st;
@@ -261,32 +268,37 @@ qmg_status solver_coarse_gmres(qmg_ctx* c, int p, void* y, const void* r, const 
   }
   st = sp.scale(sp.at(V, 0), r, a);
   if (st != QMG_OK) return st;
+  // as in the outer method the basis stays unnormalised after its first vector: the product
+  // A W_j is orthogonalised in place in the next slot, with no scaling pass, and the
+  // solution is a combination of the W_j
+  hipError_t e = launch_sig_init(dsig, iters + 1, nrhs, s);
+  if (e != hipSuccess) return hip_err(c, e, "coarse GMRES");
+  std::vector<std::vector<double>> sig(nrhs, std::vector<double>(iters + 1, 0.0));
+  for (int k = 0; k < nrhs; ++k) sig[k][0] = 1.0;
   std::vector<int> kk(nrhs, 0);
   int done_it = 0;
   for (int j = 0; j < iters; ++j) {
-    hipError_t e = launch_coarse_apply(c, p, w, sp.at(V, j), tau, nrhs, s, qform);
+    e = launch_coarse_apply(c, p, sp.at(V, j + 1), sp.at(V, j), tau, nrhs, s, qform);
     if (e != hipSuccess) return hip_err(c, e, "coarse apply");
     std::vector<std::vector<cd>> h;
-    st = sp.arnoldi(h, V, j, w);
+    st = sp.arnoldi(h, V, j, sp.at(V, j + 1), sig, dsig, iters + 1);
     if (st != QMG_OK) return st;
     bool all = true;
     for (int k = 0; k < nrhs; ++k) {
-      if (!act[k]) { a[k] = 0.0; continue; }
+      const double hn = h[k][j + 1].real();
+      sig[k][j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
+      if (!act[k]) continue;
       double est = lsq[k].update(j, h[k]);
       kk[k] = j + 1;
-      const double hn = h[k][j + 1].real();
       if (hn == 0.0 || (tol > 0 && est <= tol * beta[k])) act[k] = 0;
-      a[k] = act[k] ? 1.0 / hn : 0.0;
       all = all && !act[k];
     }
     done_it = j + 1;
     if (all || j + 1 == iters) break;
-    st = sp.scale(sp.at(V, j + 1), w, a);
-    if (st != QMG_OK) return st;
   }
   int J = 0;
   for (int k = 0; k < nrhs; ++k) J = std::max(J, kk[k]);
-  hipError_t e = launch_fill_zero(y, sp.bbytes(), s);
+  e = launch_fill_zero(y, sp.bbytes(), s);
   if (e != hipSuccess) return hip_err(c, e, "zero");
   if (J > 0) {
     std::vector<cd> coef((size_t)J * nrhs, cd(0));
@@ -461,12 +473,13 @@ qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, 
   void* Z = ws_get(c, "fg_Z", zb_full * m);
   void* f = ws_get(c, "fg_f", bb);
   void* r = ws_get(c, "fg_r", bb);
+  double* dsig = (double*)ws_get(c, "fg_dsig", sizeof(double) * (m + 1) * nrhs);
   // a reduced-precision V-cycle reads its input in its own precision: the
   // Gram-Schmidt update writes that copy of the next basis vector as it writes
   // the FP64 one, which saves the V-cycle a conversion pass over the FP64 vector
   const bool vin = prm->mg_prec != QMG_F64;
   void* vc_in = vin ? ws_get(c, "fg_vin", zb_full) : nullptr;
-  if (!V || !Z || !f || !r || (vin && !vc_in)) return set_err(c, QMG_E_NOMEM, "out of device memory (FGMRES)");
+  if (!V || !Z || !f || !r || !dsig || (vin && !vc_in)) return set_err(c, QMG_E_NOMEM, "out of device memory (FGMRES)");
   // Gamma5-preconditioned form: (D - tau Gamma5) x = Gamma5 b; q_form: (Q - tau) x = b itself
   const int mode = prm->q_form ? 1 : 0;
   hipError_t e = prm->q_form ? hipMemcpyAsync(f, b, bb, hipMemcpyDeviceToDevice, s)
@@ -584,6 +597,8 @@ qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, 
     // preconditioner takes W_j itself (flexible GMRES allows any z_j)
     std::vector<std::vector<double>> sig(na, std::vector<double>(m + 1, 0.0));
     for (int i = 0; i < na; ++i) sig[i][0] = 1.0;
+    e = launch_sig_init(dsig, m + 1, na, s);
+    if (e != hipSuccess) return hip_err(c, e, "FGMRES");
     std::vector<int> kk(na, 0);
     for (int jj = 0; jj < m; ++jj) {
       int ci = 0;
@@ -603,7 +618,8 @@ qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, 
       // solve keeps the full update, so short inner solves (the eigensolver's
       // correction equations) are unchanged by this shortcut
       const bool last = jj + 1 == m && total + 1 < prm->maxiter;
-      st = last ? sp.arnoldi_last(h, V, jj, w, &sig) : sp.arnoldi(h, V, jj, w, &sig, vin ? vc_in : nullptr, zprec);
+      st = last ? sp.arnoldi_last(h, V, jj, w, sig)
+                : sp.arnoldi(h, V, jj, w, sig, dsig, m + 1, vin ? vc_in : nullptr, zprec);
       if (st != QMG_OK) return st;
       e = mark();
       if (e != hipSuccess) return hip_err(c, e, "event");
