@@ -32,7 +32,6 @@ struct Tune {
   int sap_variant = 2;  // SAP: 0 generic kernel; 1 gathering 4^4 kernel (FP32 / BF16); 2 halo-field 4^4 kernel
   int coarse_rhs_tile = 4;                       // right-hand sides per coarse-apply work-group
   int coarse_mfma = 1;                           // MFMA coarse apply for many right-hand sides
-  int transfer_mr = 1;                           // restrict / prolong kernels sharing P loads across rhs
   int restrict_mfma_min_rhs = 4;                 // restriction on MFMA from this many rhs (1000: never)
   int ds_order = 0;  // stencil work order: 0 blocks in lexicographic order, t > 0 tiles of kTileShapes[t] blocks
   int coarse_mfma_min_rhs = 4;                   // smallest batch that takes the MFMA path

@@ -166,42 +166,64 @@ cpx<double> p[6];
   }
 }
 
-// y[k][b][o] = sum_{l,d} conj(P[b][h][j][d][l]) v[k][b][6h+d][l], o = h*ntv + j
-template <typename S, typename C>
+// y[k][b][o] = sum_{l,d} conj(P[b][h][j][d][l]) v[k][b][6h+d][l], o = h*ntv + j, for few
+// right-hand sides or small blocks: one work-group per (block, chirality, NR right-hand
+// sides), one thread per site, four columns of P in flight at a time, shared by the
+// right-hand sides; the sums over the sites run in FP64.  With the columns summed eight at a
+// time by shuffles and both chiralities in turn, 256 blocks (16^4, ntv 24, FP64, 1 rhs) took
+// 83 us; now 58, against 54 for reading P at the copy rate.
+template <typename S, typename C, int NR>
 __global__ __launch_bounds__(256) void k_restrict(Geom g, typename PT<C>::stor* y, const typename PT<S>::stor* P,
-                                                  const typename PT<S>::stor* v, int ntv, int nrhs,
-                                                  int64_t fstride, int64_t ysk, int64_t ysb) {
+                                                  const typename PT<S>::stor* v, int ntv, int nrhs, int64_t fstride) {
   using R = typename PT<S>::real;
-  extern __shared__ unsigned char smem_r[];
-  R* red = reinterpret_cast<R*>(smem_r);
-  const int b = blockIdx.x / nrhs, k = blockIdx.x % nrhs, l = threadIdx.x;
-  const int nc = 2 * ntv;
-  cpx<R> vv[12];
-  for (int c = 0; c < 12; ++c) vv[c] = ldcv<R>(v + k * fstride, sidx(g, b, c, l));
-  auto* yo = y + k * ysk + b * ysb;
+  using RC = typename PT<C>::real;
+  constexpr int NJ = 4, NV = 2 * NJ * NR;
+  __shared__ double red[2][4 * NV];
+  const int ng = (nrhs + NR - 1) / NR;
+  const int b = blockIdx.x / (2 * ng), q = blockIdx.x - b * 2 * ng, h = q & 1, k0 = (q >> 1) * NR;
+  const int l = threadIdx.x, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const bool on = l < (1 << g.bs_log);  // blocks of fewer than 64 sites leave lanes idle
+  const int nr = min(NR, nrhs - k0), nc = 2 * ntv;
+  cpx<R> vv[NR][6];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-    for (int j0 = 0; j0 < ntv; j0 += 8) {
-      R acc[16];
+  for (int r = 0; r < NR; ++r)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int j = j0 + t;
+    for (int d = 0; d < 6; ++d)
+      vv[r][d] = on && r < nr ? ldcv<R>(v + (int64_t)(k0 + r) * fstride, sidx(g, b, 6 * h + d, l)) : czero<R>();
+  int rb = 0;
+  for (int j0 = 0; j0 < ntv; j0 += NJ) {
+    double acc[NV];
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+      // columns past the last are read as the last and not stored
+      const int j = min(j0 + t, ntv - 1);
+      cpx<R> p[6];
+#pragma unroll
+      for (int d = 0; d < 6; ++d) p[d] = on ? ldcv<R>(P, pidx(g, ntv, b, h, j, d, l)) : czero<R>();
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
         cpx<R> s = czero<R>();
-        if (j < ntv)
 #pragma unroll
-          for (int d = 0; d < 6; ++d) s = s + cmul_conj(ldcv<R>(P, pidx(g, ntv, b, h, j, d, l)), vv[6 * h + d]);
-        acc[2 * t] = s.re;
-        acc[2 * t + 1] = s.im;
-      }
-      wg_sum<R, 16>(acc, red);
-      if (l < 8 && j0 + l < ntv) {
-        R re = acc[0], im = acc[1];
-#pragma unroll
-        for (int t = 1; t < 8; ++t)
-          if (t == l) { re = acc[2 * t]; im = acc[2 * t + 1]; }
-        stcv(yo, h * ntv + j0 + l, cpx<R>{re, im});
+        for (int d = 0; d < 6; ++d) cfma_conj(s, p[d], vv[r][d]);
+        acc[2 * (r * NJ + t)] = double(s.re);
+        acc[2 * (r * NJ + t) + 1] = double(s.im);
       }
     }
+    double* rd = red[rb];
+    rb ^= 1;
+    wave_fold<NV>(acc, rd + wave * NV);
+    __syncthreads();
+    if (l < NV / 2) {
+      double re = rd[2 * l], im = rd[2 * l + 1];
+      for (int w = 1; w < nw; ++w) {
+        re += rd[w * NV + 2 * l];
+        im += rd[w * NV + 2 * l + 1];
+      }
+      const int r = l / NJ, j = j0 + l % NJ;
+      if (r < nr && j < ntv)
+        stcv(y + ((int64_t)(k0 + r) * g.nb + b) * nc, h * ntv + j, cpx<RC>{RC(re), RC(im)});
+    }
+  }
 }
 
 // v[k][b][6h+d][l] = sum_j P[b][h][j][d][l] y[k][b][h*ntv+j]
@@ -210,69 +232,22 @@ __global__ __launch_bounds__(256) void k_prolong(Geom g, typename PT<S>::stor* v
                                                  const typename PT<C>::stor* y, int ntv, int nrhs,
                                                  int64_t fstride) {
   using R = typename PT<S>::real;
-  __shared__ cpx<R> ys[64];
-  const int b = blockIdx.x / nrhs, k = blockIdx.x % nrhs, l = threadIdx.x;
-  const int nc = 2 * ntv;
-  const auto* yi = y + ((int64_t)k * g.nb + b) * nc;
-  for (int o = l; o < nc; o += blockDim.x) ys[o] = ldcv<R>(yi, o);
+  __shared__ cpx<R> ys[32];
+  // one work-group per (block, chirality, right-hand side)
+  const int b = blockIdx.x / (2 * nrhs), q = blockIdx.x - b * 2 * nrhs, h = q & 1, k = q >> 1, l = threadIdx.x;
+  const auto* yi = y + ((int64_t)k * g.nb + b) * 2 * ntv + h * ntv;
+  for (int o = l; o < ntv; o += blockDim.x) ys[o] = ldcv<R>(yi, o);
   __syncthreads();
-  for (int h = 0; h < 2; ++h)
-    for (int d = 0; d < 6; ++d) {
-      cpx<R> s = czero<R>();
-      for (int j = 0; j < ntv; ++j) s = s + ldcv<R>(P, pidx(g, ntv, b, h, j, d, l)) * ys[h * ntv + j];
-      stcv(v + k * fstride, sidx(g, b, 6 * h + d, l), s);
-    }
+#pragma unroll 2
+  for (int d = 0; d < 6; ++d) {
+    cpx<R> s = czero<R>();
+#pragma unroll 8
+    for (int j = 0; j < ntv; ++j) s = s + ldcv<R>(P, pidx(g, ntv, b, h, j, d, l)) * ys[j];
+    stcv(v + k * fstride, sidx(g, b, 6 * h + d, l), s);
+  }
 }
 
-// ---- many right-hand sides: R rhs per work-group share every P load
-template <typename S, typename C, int R>
-__global__ __launch_bounds__(256) void k_restrict_mr(Geom g, typename PT<C>::stor* y, const typename PT<S>::stor* P,
-                                                     const typename PT<S>::stor* v, int ntv, int nrhs,
-                                                     int64_t fstride) {
-  using Rr = typename PT<S>::real;
-  extern __shared__ unsigned char smem_r[];
-  Rr* red = reinterpret_cast<Rr*>(smem_r);
-  const int ng = (nrhs + R - 1) / R;
-  const int b = blockIdx.x / ng, k0 = (blockIdx.x % ng) * R, l = threadIdx.x;
-  const int nr = nrhs - k0 < R ? nrhs - k0 : R;
-  const int nc = 2 * ntv;
-  cpx<Rr> vv[R][12];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int c = 0; c < 12; ++c)
-      vv[r][c] = r < nr ? ldcv<Rr>(v + (int64_t)(k0 + r) * fstride, sidx(g, b, c, l)) : czero<Rr>();
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-    for (int j0 = 0; j0 < ntv; j0 += 4) {
-      Rr acc[8 * R];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int j = j0 + t;
-        cpx<Rr> pv[6];
-#pragma unroll
-        for (int d = 0; d < 6; ++d) pv[d] = j < ntv ? ldcv<Rr>(P, pidx(g, ntv, b, h, j, d, l)) : czero<Rr>();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          cpx<Rr> sum = czero<Rr>();
-#pragma unroll
-          for (int d = 0; d < 6; ++d) sum = sum + cmul_conj(pv[d], vv[r][6 * h + d]);
-          acc[(r * 4 + t) * 2] = sum.re;
-          acc[(r * 4 + t) * 2 + 1] = sum.im;
-        }
-      }
-      wg_sum<Rr, 8 * R>(acc, red);
-      if (l < 4 * R) {
-        const int r = l / 4, t = l % 4;
-        Rr re = acc[0], im = acc[1];
-#pragma unroll
-        for (int q = 1; q < 4 * R; ++q)
-          if (q == l) { re = acc[2 * q]; im = acc[2 * q + 1]; }
-        if (r < nr && j0 + t < ntv) stcv(y + ((int64_t)(k0 + r) * g.nb + b) * nc, h * ntv + j0 + t, cpx<Rr>{re, im});
-      }
-    }
-}
-
+// ---- many right-hand sides
 // P read once per site for every rhs: the coarse inputs of the block live in LDS
 template <typename S, typename C>
 __global__ __launch_bounds__(256) void k_prolong_mr(Geom g, typename PT<S>::stor* v, const typename PT<S>::stor* P,
@@ -436,9 +411,7 @@ __global__ __launch_bounds__(256) void k_prolong_mfma(Geom g, typename PT<S>::st
 template <typename S>
 void restrict_t(const qmg_ctx* c, void* yc, const void* v, int nrhs, hipStream_t s, int p) {
   using P = typename PT<S>::stor;
-  using R = typename PT<S>::real;
   const int bs = 1 << c->g.bs_log;
-  size_t lds = sizeof(R) * 16 * std::max(bs, 4);
   if (nrhs >= c->tune.restrict_mfma_min_rhs && bs == 256 && c->ntv <= 32) {
     dim3 grid(c->g.nb, (nrhs + 15) / 16);
     const int mt = (c->ntv + 15) / 16;
@@ -455,26 +428,16 @@ void restrict_t(const qmg_ctx* c, void* yc, const void* v, int nrhs, hipStream_t
     else go(std::integral_constant<int, 2>{});
     return;
   }
-  if (nrhs > 1 && c->tune.transfer_mr) {
-    constexpr int RR = std::is_same<S, double>::value ? 2 : 4;
-    const int ng = (nrhs + RR - 1) / RR;
-    const size_t lds2 = sizeof(R) * 8 * RR * std::max(bs, 4);
-    if (p == QMG_F64)
-      hipLaunchKernelGGL((k_restrict_mr<S, double, RR>), dim3(c->g.nb * ng), dim3(bs), lds2, s, c->g, (double2*)yc,
-                         (const P*)c->P[p], (const P*)v, c->ntv, nrhs, (int64_t)field_elems(c));
-    else
-      hipLaunchKernelGGL((k_restrict_mr<S, float, RR>), dim3(c->g.nb * ng), dim3(bs), lds2, s, c->g, (float2*)yc,
-                         (const P*)c->P[p], (const P*)v, c->ntv, nrhs, (int64_t)field_elems(c));
-    return;
-  }
-  if (p == QMG_F64)
-    hipLaunchKernelGGL((k_restrict<S, double>), dim3(c->g.nb * nrhs), dim3(bs), lds, s, c->g, (double2*)yc,
-                       (const P*)c->P[p], (const P*)v, c->ntv, nrhs, (int64_t)field_elems(c),
-                       (int64_t)c->g.nb * 2 * c->ntv, (int64_t)2 * c->ntv);
-  else
-    hipLaunchKernelGGL((k_restrict<S, float>), dim3(c->g.nb * nrhs), dim3(bs), lds, s, c->g, (float2*)yc,
-                       (const P*)c->P[p], (const P*)v, c->ntv, nrhs, (int64_t)field_elems(c),
-                       (int64_t)c->g.nb * 2 * c->ntv, (int64_t)2 * c->ntv);
+  auto go = [&](auto nrc) {
+    constexpr int NR = decltype(nrc)::value;
+    const dim3 grid((unsigned)(c->g.nb * 2 * ((nrhs + NR - 1) / NR))), blk((unsigned)std::max(bs, 64));
+    using C = typename PT<S>::real;  // coarse vectors: double for FP64, else float
+    hipLaunchKernelGGL((k_restrict<S, C, NR>), grid, blk, 0, s, c->g, (typename PT<C>::stor*)yc, (const P*)c->P[p],
+                       (const P*)v, c->ntv, nrhs, (int64_t)field_elems(c));
+  };
+  if (nrhs == 1) go(std::integral_constant<int, 1>{});
+  else if (nrhs == 2 || std::is_same<S, double>::value) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, std::is_same<S, double>::value ? 2 : 4>{});
 }
 
 template <typename S>
@@ -491,7 +454,7 @@ void prolong_t(const qmg_ctx* c, void* v, const void* yc, int nrhs, hipStream_t 
                          (const float2*)yc, c->ntv, nrhs, (int64_t)field_elems(c));
     return;
   }
-  if (nrhs > 1 && c->tune.transfer_mr) {
+  if (nrhs > 1) {
     if (p == QMG_F64)
       hipLaunchKernelGGL((k_prolong_mr<S, double>), dim3(c->g.nb), dim3(bs), 0, s, c->g, (P*)v, (const P*)c->P[p],
                          (const double2*)yc, c->ntv, nrhs, (int64_t)field_elems(c));
@@ -501,10 +464,10 @@ void prolong_t(const qmg_ctx* c, void* v, const void* yc, int nrhs, hipStream_t 
     return;
   }
   if (p == QMG_F64)
-    hipLaunchKernelGGL((k_prolong<S, double>), dim3(c->g.nb * nrhs), dim3(bs), 0, s, c->g, (P*)v,
+    hipLaunchKernelGGL((k_prolong<S, double>), dim3(c->g.nb * 2 * nrhs), dim3(bs), 0, s, c->g, (P*)v,
                        (const P*)c->P[p], (const double2*)yc, c->ntv, nrhs, (int64_t)field_elems(c));
   else
-    hipLaunchKernelGGL((k_prolong<S, float>), dim3(c->g.nb * nrhs), dim3(bs), 0, s, c->g, (P*)v,
+    hipLaunchKernelGGL((k_prolong<S, float>), dim3(c->g.nb * 2 * nrhs), dim3(bs), 0, s, c->g, (P*)v,
                        (const P*)c->P[p], (const float2*)yc, c->ntv, nrhs, (int64_t)field_elems(c));
 }
 
