@@ -449,9 +449,7 @@ qmg_status qmg_set_gauge(qmg_ctx* c, const double* U, double m0, double csw, hip
   for (int p = 0; p < 3; ++p)
     if (!c->U[p] && hipMalloc(&c->U[p], nel * cbytes(p)) != hipSuccess)
       return set_err(c, QMG_E_NOMEM, "set_gauge: out of device memory");
-  QMG_TRY(hipchk(c, launch_pack_gauge(c->g, c->U[QMG_F64], U, s), "pack gauge"));
-  for (int p = 1; p < 3; ++p)
-    QMG_TRY(hipchk(c, launch_convert(c->U[p], p, c->U[QMG_F64], QMG_F64, (int64_t)nel, s), "convert gauge"));
+  QMG_TRY(hipchk(c, launch_pack_gauge(c->g, c->U, U, s), "pack gauge"));
   c->clover = csw != 0.0;
   if (c->clover) {
     for (int p = 0; p < 3; ++p)

@@ -3,33 +3,63 @@
 
 namespace {
 
+// 256 sites in block order per work-group, transposed through LDS: the canonical side is
+// read and written in runs of a block's last direction (768 B for 4^4 blocks), the internal
+// side in rows of sites.  With one thread walking its site's 192 B the canonical accesses
+// were 16 B apart by 192: 32x16^3 FP64 pack 16.8 -> 15.1 us, unpack 21.5 -> 10.6.
+constexpr int kTile = 256, kRow = kTile + 1;
+
 template <typename S>
 __global__ __launch_bounds__(256) void k_pack(Geom g, typename PT<S>::stor* out, const double2* canon) {
-  int64_t site = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (site >= g.V) return;
-  int k = blockIdx.y;
-  int b = (int)(site >> g.bs_log), l = (int)(site & ((1 << g.bs_log) - 1));
-  int64_t cs = canon_site(g, b, l);
-  const double2* src = canon + ((int64_t)k * g.V + cs) * 12;
-  auto* dst = out + (int64_t)k * g.V * 12;
+  __shared__ double2 sh[12 * kRow];
+  const int64_t s0 = (int64_t)blockIdx.x * kTile;
+  const int ns = (int)min((int64_t)kTile, g.V - s0);
+  const double2* src = canon + (int64_t)blockIdx.y * g.V * 12;
+  auto* dst = out + (int64_t)blockIdx.y * g.V * 12;
+  double2 v[12];  // all loads in flight together
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const int e = min((int)threadIdx.x + 256 * k, 12 * ns - 1), c = e % 12;
+    const int64_t site = s0 + e / 12;
+    v[k] = src[canon_site(g, (int)(site >> g.bs_log), (int)(site & ((1 << g.bs_log) - 1))) * 12 + c];
+  }
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const int e = min((int)threadIdx.x + 256 * k, 12 * ns - 1);
+    sh[(e % 12) * kRow + e / 12] = v[k];
+  }
+  __syncthreads();
+  const int i = threadIdx.x;
+  if (i >= ns) return;
+  const int b = (int)((s0 + i) >> g.bs_log), l = (int)((s0 + i) & ((1 << g.bs_log) - 1));
+#pragma unroll
   for (int c = 0; c < 12; ++c) {
-    double2 v = src[c];
+    const double2 v = sh[c * kRow + i];
     stcv(dst, sidx(g, b, c, l), cpx<double>{v.x, v.y});
   }
 }
 
 template <typename S>
 __global__ __launch_bounds__(256) void k_unpack(Geom g, double2* canon, const typename PT<S>::stor* in) {
-  int64_t site = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (site >= g.V) return;
-  int k = blockIdx.y;
-  int b = (int)(site >> g.bs_log), l = (int)(site & ((1 << g.bs_log) - 1));
-  int64_t cs = canon_site(g, b, l);
-  double2* dst = canon + ((int64_t)k * g.V + cs) * 12;
-  const auto* src = in + (int64_t)k * g.V * 12;
-  for (int c = 0; c < 12; ++c) {
-    cpx<double> v = ldcv<double>(src, sidx(g, b, c, l));
-    dst[c] = make_double2(v.re, v.im);
+  __shared__ double2 sh[12 * kRow];
+  const int64_t s0 = (int64_t)blockIdx.x * kTile;
+  const int ns = (int)min((int64_t)kTile, g.V - s0);
+  double2* dst = canon + (int64_t)blockIdx.y * g.V * 12;
+  const auto* src = in + (int64_t)blockIdx.y * g.V * 12;
+  const int t = threadIdx.x;
+  if (t < ns) {
+    const int b = (int)((s0 + t) >> g.bs_log), l = (int)((s0 + t) & ((1 << g.bs_log) - 1));
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      const cpx<double> v = ldcv<double>(src, sidx(g, b, c, l));
+      sh[c * kRow + t] = make_double2(v.re, v.im);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 12 * ns; e += 256) {
+    const int i = e / 12, c = e - 12 * i;
+    const int64_t site = s0 + i;
+    dst[canon_site(g, (int)(site >> g.bs_log), (int)(site & ((1 << g.bs_log) - 1))) * 12 + c] = sh[c * kRow + i];
   }
 }
 

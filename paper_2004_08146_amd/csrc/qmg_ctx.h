@@ -118,7 +118,8 @@ hipError_t launch_pack(const Geom& g, void* out, int p, const double* canon, int
 hipError_t launch_unpack(const Geom& g, double* canon, const void* in, int p, int nrhs, hipStream_t s);
 hipError_t launch_convert(void* dst, int pd, const void* src, int ps, int64_t n, hipStream_t s);
 // ---- gauge.hip
-hipError_t launch_pack_gauge(const Geom& g, void* U64, const double* canon, hipStream_t s);
+// links in the three storage types
+hipError_t launch_pack_gauge(const Geom& g, void* const U[3], const double* canon, hipStream_t s);
 hipError_t launch_clover(const Geom& g, void* diag64, const void* U64, double m0, double csw,
                          hipStream_t s);
 // ---- dslash.hip   mode 0: (D - tau Gamma5), mode 1: (Gamma5 D - tau)
