@@ -18,6 +18,9 @@
 
 namespace {
 
+// coarse vectors are held in FP64 with FP64 blocks, in FP32 otherwise
+template <typename S> using CT = typename PT<S>::real;
+
 struct TauArr {
   double t[QMG_MAXRHS];
   int qform;  // 1: Gamma5^c (D_c - tau Gamma5^c) = Gamma5^c D_c - tau, the Galerkin P^H (Q - tau) P
@@ -25,7 +28,7 @@ struct TauArr {
 
 // Few right-hand sides: one work-group per coarse site, wave d takes stencil entry d (the
 // nine are summed through LDS), lane i row i.  One wave doing the nine in turn left a
-// launch waiting for its loads: 41 us for 256 sites (ntv 24, FP64, 1 rhs), now 24, bound by
+// launch waiting for its loads: 41 us for 256 sites (ntv 24, FP64, 1 rhs), now 20, bound by
 // the row-wise reads of the four backward blocks.
 template <typename S, typename C, int T>
 __global__ __launch_bounds__(576) void k_coarse_apply(const int* nbr, int nb, typename PT<C>::stor* out,
@@ -87,11 +90,8 @@ __global__ __launch_bounds__(576) void k_coarse_apply(const int* nbr, int nb, ty
   }
 }
 
-// ---- MFMA coarse apply (many right-hand sides): per coarse site b and tile of
-// 16 rhs, Out (2ntv x 16) = sum_d D_c[b][d] (2ntv x 2ntv) In_{nbr(b,d)} (2ntv x 16),
-// a complex GEMM done as four real 16x16x4 MFMA products per k-step
-// (C_re += A_re B_re - A_im B_im, C_im += A_re B_im + A_im B_re).  One wave
-// per work-group; the 16 rhs of a neighbour block are staged in LDS.
+// ---- MFMA coarse apply: per coarse site b and tile of 16 columns, Out (2ntv x 16) =
+// sum_d D_c[b][d] (2ntv x 2ntv) In_{nbr(b,d)} (2ntv x 16).
 typedef float mf4 __attribute__((ext_vector_type(4)));
 typedef double md4 __attribute__((ext_vector_type(4)));
 
@@ -107,85 +107,147 @@ template <typename R> __device__ __forceinline__ int mrow(int l, int r);
 template <> __device__ __forceinline__ int mrow<float>(int l, int r) { return 4 * (l >> 4) + r; }
 template <> __device__ __forceinline__ int mrow<double>(int l, int r) { return 4 * r + (l >> 4); }
 
-template <typename S, typename C, int NT>
-__global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, const int* ord, int nb, typename PT<C>::stor* out,
-                                                         const typename PT<S>::stor* DcT, const typename PT<C>::stor* in,
-                                                         int nrhs, TauArr tau) {
-  using R = typename PT<C>::real;
+// four consecutive stored entries, as wide loads
+__device__ __forceinline__ void ld4s(const double2* p, double2* f) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) f[q] = p[q];
+}
+__device__ __forceinline__ void ld4s(const float2* p, float2* f) {
+  const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+  f[0] = {a.x, a.y}, f[1] = {a.z, a.w}, f[2] = {b.x, b.y}, f[3] = {b.z, b.w};
+}
+__device__ __forceinline__ void ld4s(const uint32_t* p, uint32_t* f) {
+  const uint4 a = reinterpret_cast<const uint4*>(p)[0];
+  f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w;
+}
+
+// One wave per 16-row tile t, the waves share the staged inputs.  PACK: up to 8 right-hand sides, columns 0-7 their real parts and
+// 8-15 their imaginary parts, two real products per step of 4 (the staged pair is (re, -im)
+// or (im, re)); else 16 right-hand sides per tile and four products.
+// Backward blocks: sum_j g_i g_j conj(F_ji) y_j = g_i conj(sum_j F_ji conj(g_j y_j)), so the
+// staged input takes g_j and the conjugation and the sum, kept apart, the rest.
+// Each run of 16 contraction indices goes in the order j = jb + 4 lk + q (step q): a lane's
+// four inputs, and its four entries of a backward block, are consecutive.  The blocks and
+// inputs of the next entry are loaded while this one is multiplied.  Inputs staged with the
+// right-hand side fastest, so that all writes of a wave met in one LDS bank, no loads ahead
+// and four products for any batch took, 32^4 (4096 sites), ntv 24: FP32 8 rhs 138 us, 11 rhs
+// 142; FP64 8 rhs 252; bf16 8 rhs 119; 16^4 FP32 8 rhs 23.7.  Now 100, 121, 197, 64 and 12.0.
+// Bound: the nine blocks per site, 7 TB/s through the fabric (a forward block that another
+// XCD reads as a backward one is read twice); with 9-16 rhs also the FP32 matrix rate (69 us).
+// Three groups of waves on three entries each gained nothing: 8 rhs FP32 159 us.
+template <typename S, int NT, bool PACK>
+__global__ __launch_bounds__(64 * NT) void k_coarse_mfma(const int* nbr, const int* ord, int nb,
+                                                         typename PT<CT<S>>::stor* out,
+                                                         const typename PT<S>::stor* DcT,
+                                                         const typename PT<CT<S>>::stor* in, int nrhs, TauArr tau) {
+  using R = CT<S>;
   using AT = typename MAcc<R>::T;
-  constexpr int NC = 16 * NT;  // 2 ntv
-  __shared__ cpx<R> Bs[NC][16];
-  __shared__ cpx<R> Bself[NC][16];
-  // one wave per 16-row tile t of the output; the waves share the staged inputs
+  constexpr int NC = 16 * NT;               // 2 ntv
+  constexpr int NR = PACK ? 8 : 16;         // right-hand sides of a work-group
+  constexpr int LD = NC + (sizeof(R) == 8 ? 1 : 2);  // row stride: no bank shared by 16 lanes' 16 bytes
+  constexpr int NA = PACK ? 1 : 2;          // accumulators: (re | im), or re and im
+  __shared__ cpx<R> Bs[2][16][LD];
   // each XCD walks a contiguous share of the sites in lexicographic order, so that a forward
   // block is still in its L2 when the neighbour reads it as a backward block (in colour order
   // that neighbour ran half a launch later: 32^4, FP32, 8 rhs 153 -> 140 us)
   const int L = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-  const int b = ord ? ord[L] : L, n0 = blockIdx.y * 16, tid = threadIdx.x;
-  const int t = tid >> 6, l = tid & 63;
+  const int b = ord ? ord[L] : L, n0 = blockIdx.y * NR;
+  const int tid = threadIdx.x, t = tid >> 6, l = tid & 63;
   const int ln = l & 15, lk = l >> 4;
-  AT acc_re = AT{0, 0, 0, 0}, acc_im = AT{0, 0, 0, 0};
-  // output row of this lane's A fragment
   const int irow = 16 * t + ln;
-#pragma unroll 1
-  for (int d = 0; d < 9; ++d) {
+  const int sj = tid % NC, sn = tid / NC;  // staging: entry sj of rhs sn + 4 e
+  const R gj = sj < NC / 2 ? R(1) : R(-1);
+
+  AT af[NA], ab[NA];
+#pragma unroll
+  for (int k = 0; k < NA; ++k) af[k] = ab[k] = AT{0, 0, 0, 0};
+  typename PT<S>::stor ar[NC / 4], an[NC / 4];
+  cpx<R> br[NR / 4];
+
+  auto load = [&](int d, typename PT<S>::stor (&f)[NC / 4]) {
     const int nbk = d == 0 ? b : nbr[b * 8 + d - 1];
-    __syncthreads();
-    for (int idx = tid; idx < NC * 16; idx += 64 * NT) {
-      const int j = idx % NC, n = idx / NC;
-      const cpx<R> v = n0 + n < nrhs ? ldcv<R>(in, ((int64_t)(n0 + n) * nb + nbk) * NC + j) : czero<R>();
-      Bs[j][n] = v;
-      if (d == 0) Bself[j][n] = v;
+#pragma unroll
+    for (int e = 0; e < NR / 4; ++e) {
+      const int n = n0 + sn + 4 * e;
+      br[e] = n < nrhs ? ldcv<R>(in, ((int64_t)n * nb + nbk) * NC + sj) : czero<R>();
     }
-    __syncthreads();
     if (d == 0 || (d & 1)) {
-      // self or forward block: A_{ij} at row j of the transposed block
-      const auto* Dd = DcT + ((int64_t)b * 5 + (d + 1) / 2) * NC * NC + irow;
-#pragma unroll 4
-      for (int j0 = 0; j0 < NC; j0 += 4) {
-        const cpx<R> bv = Bs[j0 + lk][ln];
-        const cpx<R> av = ldcv<R>(Dd, (int64_t)(j0 + lk) * NC);
-        acc_re = mfma(av.re, bv.re, acc_re);
-        acc_re = mfma(-av.im, bv.im, acc_re);
-        acc_im = mfma(av.re, bv.im, acc_im);
-        acc_im = mfma(av.im, bv.re, acc_im);
-      }
+      // self or forward block: A_ij at row j of the transposed block
+      const auto* Dd = DcT + ((int64_t)b * 5 + (d + 1) / 2) * NC * NC + (4 * lk) * NC + irow;
+#pragma unroll
+      for (int j = 0; j < NC / 4; ++j) f[j] = Dd[((j >> 2) * 16 + (j & 3)) * NC];
     } else {
-      // backward block from the forward block F of the site at X - mu:
-      // A_{ij} = g_i g_j conj(F_{ji}), F_{ji} stored at i * NC + j, i.e. along row i.
-      // The contraction index is visited in a permuted order (A and B permuted
-      // alike): in each run of 16 columns, MFMA step s takes j = jb + 4 lk + s, so
-      // every lane reads its 4 consecutive entries of row i with one wide load
-      const auto* Fd = DcT + ((int64_t)nbk * 5 + d / 2) * NC * NC + (int64_t)irow * NC;
-      const R gi = irow < NC / 2 ? R(1) : R(-1);
+      // forward block F of the site at X - mu: F_ji at row i
+      const auto* Fd = DcT + ((int64_t)nbk * 5 + d / 2) * NC * NC + irow * NC + 4 * lk;
 #pragma unroll
-      for (int jb = 0; jb < NC; jb += 16) {
-        cpx<R> f[4];
-        ld4c(Fd + jb + 4 * lk, f);
-        const R gg = (jb + 4 * lk < NC / 2) ? gi : -gi;  // the 4 columns share a chirality half
+      for (int j = 0; j < NC / 4; j += 4) ld4s(Fd + 4 * j, f + j);
+    }
+  };
+  auto stage = [&](int d, int buf) {
+    const bool fwd = d == 0 || (d & 1);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const cpx<R> bv = Bs[jb + 4 * lk + q][ln];
-          const R are = gg * f[q].re, aim = -gg * f[q].im;
-          acc_re = mfma(are, bv.re, acc_re);
-          acc_re = mfma(-aim, bv.im, acc_re);
-          acc_im = mfma(are, bv.im, acc_im);
-          acc_im = mfma(aim, bv.re, acc_im);
-        }
+    for (int e = 0; e < NR / 4; ++e) {
+      const int n = sn + 4 * e;
+      const cpx<R> v = fwd ? br[e] : cpx<R>{gj * br[e].re, -gj * br[e].im};
+      if constexpr (PACK) {
+        Bs[buf][n][sj] = {v.re, -v.im};
+        Bs[buf][n + 8][sj] = {v.im, v.re};
+      } else {
+        Bs[buf][n][sj] = v;
       }
+    }
+  };
+  auto mult = [&](int buf, AT (&acc)[NA]) {
+#pragma unroll
+    for (int j = 0; j < NC / 4; ++j) {
+      const cpx<R> a = ldcv<R>(ar, j);
+      const cpx<R> v = Bs[buf][ln][(j >> 2) * 16 + 4 * lk + (j & 3)];
+      if constexpr (PACK) {
+        acc[0] = mfma(a.re, v.re, acc[0]);
+        acc[0] = mfma(a.im, v.im, acc[0]);
+      } else {
+        acc[0] = mfma(a.re, v.re, acc[0]);
+        acc[1] = mfma(a.re, v.im, acc[1]);
+        acc[0] = mfma(a.im, -v.im, acc[0]);
+        acc[1] = mfma(a.im, v.re, acc[1]);
+      }
+    }
+  };
+
+  load(1, ar);
+  stage(1, 0);
+#pragma unroll
+  for (int s = 0; s < 9; ++s) {
+    const int d = (s + 1) % 9, dn = (s + 2) % 9;  // the site itself last
+    __syncthreads();
+    if (s < 8) load(dn, an);
+    if (d == 0 || (d & 1)) mult(s & 1, af);
+    else mult(s & 1, ab);
+    if (s < 8) {
+      stage(dn, (s + 1) & 1);
+#pragma unroll
+      for (int j = 0; j < NC / 4; ++j) ar[j] = an[j];
     }
   }
-  const int n = n0 + ln;
-  if (n >= nrhs) return;
-  const R tn = R(tau.t[n]);
+
+  const int n = PACK ? n0 + (ln & 7) : n0 + ln;
+  const R tn = n < nrhs ? R(tau.t[n]) : R(0);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 16 * t + mrow<R>(l, r);
     const R g5 = i < NC / 2 ? R(1) : R(-1);
-    const cpx<R> self = Bself[i][ln];
-    cpx<R> v = {acc_re[r] - tn * g5 * self.re, acc_im[r] - tn * g5 * self.im};
+    cpx<R> v, self = Bs[0][PACK ? ln & 7 : ln][i];
+    if constexpr (PACK) {
+      const R x = af[0][r] + (ln < 8 ? g5 : -g5) * ab[0][r], o = __shfl_xor(x, 8);
+      v = ln < 8 ? cpx<R>{x, o} : cpx<R>{o, x};
+      self.im = -self.im;
+    } else {
+      v = {af[0][r] + g5 * ab[0][r], af[1][r] - g5 * ab[1][r]};
+    }
+    v = {v.re - tn * g5 * self.re, v.im - tn * g5 * self.im};
     if (tau.qform) v = g5 * v;
-    stcv(out, ((int64_t)n * nb + b) * NC + i, v);
+    // packed: the two lanes of an entry store two of the four rows each
+    if (n < nrhs && (!PACK || (ln >> 3) == (r >> 1))) stcv(out, ((int64_t)n * nb + b) * NC + i, v);
   }
 }
 
@@ -198,58 +260,49 @@ struct CLevel {
   const void* D;
 };
 
-template <typename S>
-void capply_mfma(const CLevel& lv, int p, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
-  using P = typename PT<S>::stor;
-  dim3 grid(lv.nb, (nrhs + 15) / 16);
-  // 2 ntv = 48 (ntv = 24) -> 3 row tiles; 2 ntv = 32 -> 2; 2 ntv = 16 -> 1
-  const int nt = (2 * lv.ntv) / 16;
-  auto go = [&](auto ntc) {
-    constexpr int NT = decltype(ntc)::value;
-    if (p == QMG_F64)
-      hipLaunchKernelGGL((k_coarse_mfma<S, double, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.ord, lv.nb, (double2*)out,
-                         (const P*)lv.D, (const double2*)in, nrhs, tau);
-    else
-      hipLaunchKernelGGL((k_coarse_mfma<S, float, NT>), grid, dim3(64 * NT), 0, s, lv.nbr, lv.ord, lv.nb, (float2*)out,
-                         (const P*)lv.D, (const float2*)in, nrhs, tau);
-  };
-  if (nt == 3) go(std::integral_constant<int, 3>{});
-  else if (nt == 2) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 1>{});
+template <typename S, int NT>
+void capply_mfma(const CLevel& lv, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
+  using P = typename PT<CT<S>>::stor;
+  const auto* D = (const typename PT<S>::stor*)lv.D;
+  if (nrhs <= 8)
+    hipLaunchKernelGGL((k_coarse_mfma<S, NT, true>), dim3(lv.nb), dim3(64 * NT), 0, s, lv.nbr, lv.ord, lv.nb, (P*)out, D,
+                       (const P*)in, nrhs, tau);
+  else
+    hipLaunchKernelGGL((k_coarse_mfma<S, NT, false>), dim3(lv.nb, (nrhs + 15) / 16), dim3(64 * NT), 0, s, lv.nbr, lv.ord,
+                       lv.nb, (P*)out, D, (const P*)in, nrhs, tau);
 }
 
 template <typename S, int T>
-void capply_t(const CLevel& lv, int p, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
-  using P = typename PT<S>::stor;
+void capply_t(const CLevel& lv, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
+  using P = typename PT<CT<S>>::stor;
   const int nc = 2 * lv.ntv;
-  dim3 grid(lv.nb, (nrhs + T - 1) / T);
-  if (p == QMG_F64)
-    hipLaunchKernelGGL((k_coarse_apply<S, double, T>), grid, dim3(576), 0, s, lv.nbr, lv.nb, (double2*)out,
-                       (const P*)lv.D, (const double2*)in, nc, nrhs, tau);
-  else
-    hipLaunchKernelGGL((k_coarse_apply<S, float, T>), grid, dim3(576), 0, s, lv.nbr, lv.nb, (float2*)out,
-                       (const P*)lv.D, (const float2*)in, nc, nrhs, tau);
+  hipLaunchKernelGGL((k_coarse_apply<S, CT<S>, T>), dim3(lv.nb, (nrhs + T - 1) / T), dim3(576), 0, s, lv.nbr, lv.nb,
+                     (P*)out, (const typename PT<S>::stor*)lv.D, (const P*)in, nc, nrhs, tau);
 }
 
 template <typename S>
-void capply_s(const qmg_ctx* c, const CLevel& lv, int p, void* out, const void* in, const double* htau, int nrhs,
+void capply_s(const qmg_ctx* c, const CLevel& lv, void* out, const void* in, const double* htau, int nrhs,
               hipStream_t s, int qform) {
   TauArr t;
   for (int i = 0; i < QMG_MAXRHS; ++i) t.t[i] = i < nrhs ? htau[i] : 0.0;
   t.qform = qform;
-  // MFMA path when the coarse dimension is a multiple of 16 (ntv = 8, 16, 24) and
-  // enough right-hand sides share each matrix block
-  if (c->tune.coarse_mfma && (2 * lv.ntv) % 16 == 0 && 2 * lv.ntv <= 48 && nrhs >= c->tune.coarse_mfma_min_rhs) {
-    if constexpr (std::is_same<S, double>::value) {
-      if (p == QMG_F64) { capply_mfma<S>(lv, p, out, in, t, nrhs, s); return; }
-    } else {
-      capply_mfma<S>(lv, p, out, in, t, nrhs, s);
-      return;
-    }
+  // The matrix-core kernel takes rows in whole tiles of 16 (ntv = 8, 16, 24).  It has the
+  // blocks of the next entry in flight and wins wherever the launch is bound by reading them;
+  // with one or two right-hand sides and few sites one wave per entry has the shorter chain.
+  // 1 rhs, ntv 24, the other kernel against it: FP64 16 sites (3 MB of blocks) 10.5 / 13.5 us,
+  // 128 sites (24 MB) 16.7 / 14.0; FP32 512 sites (47 MB) 12.5 / 13.9, 1024 sites (94 MB)
+  // 25.2 / 22.6; bf16 1024 sites (47 MB) 14.6 / 17.5, 2048 sites (94 MB) 31.1 / 31.1.
+  // 3 rhs, 16 sites: FP64 15.6 / 14.2, FP32 12.5 / 10.3.
+  const int64_t bytes = (int64_t)lv.nb * 5 * 4 * lv.ntv * lv.ntv * sizeof(typename PT<S>::stor);
+  const bool many = nrhs >= 3 || bytes > (std::is_same<S, double>::value ? 16 : 64) * (int64_t(1) << 20);
+  if (c->tune.coarse_mfma && many) {
+    if (lv.ntv == 24) return capply_mfma<S, 3>(lv, out, in, t, nrhs, s);
+    if (lv.ntv == 16) return capply_mfma<S, 2>(lv, out, in, t, nrhs, s);
+    if (lv.ntv == 8) return capply_mfma<S, 1>(lv, out, in, t, nrhs, s);
   }
-  if (nrhs >= 3) capply_t<S, 4>(lv, p, out, in, t, nrhs, s);
-  else if (nrhs == 2) capply_t<S, 2>(lv, p, out, in, t, nrhs, s);
-  else capply_t<S, 1>(lv, p, out, in, t, nrhs, s);
+  if (nrhs >= 3) capply_t<S, 4>(lv, out, in, t, nrhs, s);
+  else if (nrhs == 2) capply_t<S, 2>(lv, out, in, t, nrhs, s);
+  else capply_t<S, 1>(lv, out, in, t, nrhs, s);
 }
 
 }  // namespace
@@ -258,9 +311,9 @@ void capply_s(const qmg_ctx* c, const CLevel& lv, int p, void* out, const void* 
 hipError_t launch_coarse_apply(const qmg_ctx* c, int p, void* out, const void* in, const double* dtau, int nrhs,
                                hipStream_t s, int qform) {
   const CLevel lv{c->g.nbr, c->g.lexord, c->g.nb, c->ntv, c->Dc[p]};
-  if (p == QMG_F64) capply_s<double>(c, lv, p, out, in, dtau, nrhs, s, qform);
-  else if (p == QMG_F32) capply_s<float>(c, lv, p, out, in, dtau, nrhs, s, qform);
-  else capply_s<bf16_t>(c, lv, p, out, in, dtau, nrhs, s, qform);
+  if (p == QMG_F64) capply_s<double>(c, lv, out, in, dtau, nrhs, s, qform);
+  else if (p == QMG_F32) capply_s<float>(c, lv, out, in, dtau, nrhs, s, qform);
+  else capply_s<bf16_t>(c, lv, out, in, dtau, nrhs, s, qform);
   return hipGetLastError();
 }
 
@@ -269,7 +322,7 @@ hipError_t launch_apply_l3(const qmg_ctx* c, int p, void* out, const void* in, c
                            hipStream_t s, int qform) {
   const int sp = p == QMG_F64 ? 0 : 1;
   const CLevel lv{c->l3.nbr3, nullptr, c->l3.n3, c->l3.ntv2, c->l3.D3[sp]};
-  if (p == QMG_F64) capply_s<double>(c, lv, p, out, in, dtau, nrhs, s, qform);
-  else capply_s<float>(c, lv, p, out, in, dtau, nrhs, s, qform);
+  if (p == QMG_F64) capply_s<double>(c, lv, out, in, dtau, nrhs, s, qform);
+  else capply_s<float>(c, lv, out, in, dtau, nrhs, s, qform);
   return hipGetLastError();
 }

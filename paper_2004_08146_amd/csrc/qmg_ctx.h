@@ -34,7 +34,6 @@ struct Tune {
   int coarse_mfma = 1;                           // MFMA coarse apply for many right-hand sides
   int restrict_mfma_min_rhs = 4;                 // restriction on MFMA from this many rhs (1000: never)
   int ds_order = 0;  // stencil work order: 0 blocks in lexicographic order, t > 0 tiles of kTileShapes[t] blocks
-  int coarse_mfma_min_rhs = 4;                   // smallest batch that takes the MFMA path
   bool tuned = false;
 };
 

@@ -67,3 +67,33 @@ def test_field_dot_remainder(dims, prec):
     for k in range(3):
         scale = np.linalg.norm(av[k]) * np.linalg.norm(bv[k])
         assert abs(got[k] - np.vdot(av[k], bv[k])) < 1e-12 * scale
+
+
+# matrix-core apply: 2 ntv in one, two and three tiles of 16 rows, both packings (up to 8 and
+# up to 16 right-hand sides) at their edges, 256 sites where one and two right-hand sides take
+# it too; rel. 1e-13 (FP64: sums of 9 * 48 products),
+# 9 * 48 * 2^-24 = 2.6e-5 (FP32: rounding of blocks, inputs and every partial sum)
+@pytest.mark.parametrize("dims,block,ntv,nrhs", [
+    ((8, 8, 8, 8), (4, 4, 4, 4), 8, 3), ((8, 8, 8, 8), (4, 4, 4, 4), 16, 8), ((8, 8, 8, 8), (4, 4, 4, 4), 24, 9),
+    ((8, 8, 8, 8), (4, 4, 4, 4), 24, 16), ((8, 8, 8, 8), (4, 4, 4, 4), 16, 17), ((8, 8, 8, 8), (2, 2, 2, 2), 24, 1),
+    ((8, 8, 8, 8), (2, 2, 2, 2), 24, 2)])
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-13), ("f32", 2.6e-5)])
+def test_coarse_apply_matrix_cores(dims, block, ntv, nrhs, prec, tol):
+    case("coarse apply %s ntv %d nrhs %d %s" % (dims, ntv, nrhs, prec))
+    qmg = need_gpu()
+    U = random_links(dims, 0.5, seed_for(2, "U"))
+    op = dirac.Operator(U, -0.8, oclover.clover_term(U, 1.0))
+    lat = qmg.Lattice(dims, block)
+    lat.set_gauge(dev(U), -0.8, 1.0)
+    W = random_test_vectors(dims, ntv, seed_for(2, "W"))
+    lat.set_test_vectors(lat.pack(dev(W)), ntv)
+    h, order = mg.TwoLevel(op, list(W), block), lat.coarse_site_order()
+    rng = np.random.default_rng(8)
+    y = rng.standard_normal((nrhs, len(order), 2 * ntv)) + 1j * rng.standard_normal((nrhs, len(order), 2 * ntv))
+    taus = [0.02 * (k + 1) for k in range(nrhs)]
+    real = np.float64 if prec == "f64" else np.float32
+    yd = dev(lex_to_coarse(y, order).view(np.float64).astype(real))
+    og = lat.apply_coarse(lat.coarse(nrhs, prec), yd, taus, nrhs, prec)
+    out = coarse_to_lex(host(og).view(real).astype(np.float64).view(np.complex128), order, ntv)
+    for k in range(nrhs):
+        assert rel_err(out[k], h.coarse.apply(y[k], taus[k])) < tol
