@@ -4,8 +4,9 @@
 //   e_i = n_mr minimal-residual steps on A_{tau,i} e = r_i from e = 0
 //         (A_{tau,i}: A_tau restricted to block i, hops leaving it dropped),
 //   x_i += e_i.
-// Blocks of one colour do not touch each other, so each block is one
-// work-group (one thread per site); the residual needs x of the neighbouring
+// Blocks of one colour do not touch each other, so a block and right-hand side
+// are one work-group (one thread per site), or one of several slots of a wave if
+// the block has fewer than 64 sites; the residual needs x of the neighbouring
 // (other-colour) blocks, which this launch does not modify.  The block
 // iterate rho lives in LDS so the block operator reads its neighbours there;
 // block-wide dot products use a fixed reduction order (bitwise reproducible).
@@ -29,36 +30,30 @@ struct SapArgs {
   double tau[QMG_MAXRHS];
 };
 
-// sum of NV values over the work-group, same result in every thread
+// sum of NV values over the 2^bs_log lanes of a slot (within a wave or whole waves), same
+// result in every thread
 template <typename R, int NV>
-__device__ __forceinline__ void block_sum(R (&v)[NV], R* red) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  if (nt >= 64) {
-    const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+__device__ __forceinline__ void slot_sum(R (&v)[NV], R* red, int bs_log) {
+  if (bs_log < 6) {
+    for (int m = 1; m < 1 << bs_log; m <<= 1)
 #pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
-    if (lane == 0)
-#pragma unroll
-      for (int i = 0; i < NV; ++i) red[wave * NV + i] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      R s = red[i];
-      for (int w = 1; w < nw; ++w) s += red[w * NV + i];
-      v[i] = s;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) red[i * nt + tid] = v[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      R s = red[i * nt];
-      for (int t = 1; t < nt; ++t) s += red[i * nt + t];
-      v[i] = s;
-    }
+      for (int i = 0; i < NV; ++i) v[i] += __shfl_xor(v[i], m);
+    return;
   }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
+  const int wave = threadIdx.x >> 6, nw = 1 << (bs_log - 6);
+  if (nw == 1) return;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) red[wave * NV + i] = v[i];
   __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    R s = red[i];
+    for (int w = 1; w < nw; ++w) s += red[w * NV + i];
+    v[i] = s;
+  }
 }
 
 template <typename R>
@@ -71,104 +66,218 @@ __device__ __forceinline__ Spinor<R> lds_spinor(const cpx<R>* sh, int l, int bs)
   return p;
 }
 
-template <typename R, typename P, bool CLOVER>
-__device__ __forceinline__ Spinor<R> diag_part(const P* diag, R mass4, const Geom& g, int b, int l,
-                                               const Spinor<R>& v, R tau) {
-  Spinor<R> o;
-  if (CLOVER) o = apply_diag<R>(diag, g, b, l, v);
-  else {
+// keeps values derived from v from being computed once outside a loop and held in registers
+template <typename T>
+__device__ __forceinline__ T opaque(T v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// components of the site at element `at` of an array with rows of 1 << lg, as stored
+template <int N, typename P>
+__device__ __forceinline__ void far_rows(P (&v)[N], const P* f, int64_t at, int lg) {
+  const P* q = f + at;
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+  for (int i = 0; i < N; ++i) v[i] = q[(int64_t)i << lg];
+}
+// the same with a 32-bit offset from the work-group's own place
+template <int N, typename P>
+__device__ __forceinline__ void near_rows(P (&v)[N], const P* f, uint32_t at, int lg) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) o.s[s][c] = mass4 * v.s[s][c];
-  }
+  for (int i = 0; i < N; ++i) v[i] = ldo(f + ((size_t)i << lg), at);
+}
+template <typename R, typename P>
+__device__ __forceinline__ cpx<R> as_cpx(P v) {
+  const auto w = cv(v);
+  return cpx<R>{R(w.re), R(w.im)};
+}
+template <typename R, typename P>
+__device__ __forceinline__ Spinor<R> as_spinor(const P (&v)[12]) {
+  Spinor<R> p;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) p.s[i / 3][i % 3] = as_cpx<R>(v[i]);
+  return p;
+}
+template <typename R, typename P>
+__device__ __forceinline__ Link<R> as_link(const P (&v)[9]) {
+  Link<R> u;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) u.u[i / 3][i % 3] = as_cpx<R>(v[i]);
+  return u;
+}
+
+// the sums so far are formed here: their operands are not kept for later
+template <typename R>
+__device__ __forceinline__ void pin(Spinor<R>& p) {
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) o.s[s][c] = (s < 2) ? o.s[s][c] - tau * v.s[s][c] : o.s[s][c] + tau * v.s[s][c];
-  return o;
+    for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(p.s[s][c].re), "+v"(p.s[s][c].im));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// clover block of one chirality as stored; D: the clover blocks of the work-group's blocks
+template <int H, typename P>
+__device__ __forceinline__ void fetch_diag(P (&d)[18], const P* D, uint32_t at, int lg) {
+  near_rows(d, D + ((size_t)(18 * H) << lg), at, lg);
+}
+
+// o = (m0 + 4 + C - tau Gamma5) v - 1/2 acc, chirality H
+template <typename R, int H, bool CLOVER, typename P>
+__device__ __forceinline__ void diag_part(Spinor<R>& o, const P (&dr)[18], R mass4, const Spinor<R>& v, R tau,
+                                          const Spinor<R>& acc) {
+  const R t = H == 0 ? -tau : tau;
+  cpx<R> w[6];
+  if (CLOVER) {
+    cpx<R> in[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      in[i] = v.s[2 * H + i / 3][i % 3];
+      const cpx<R> d = as_cpx<R>(dr[i / 2]);
+      w[i] = (i % 2 == 0 ? d.re : d.im) * in[i];
+    }
+    int k = 3;
+#pragma unroll
+    for (int i = 1; i < 6; ++i)
+#pragma unroll
+      for (int j = 0; j < i; ++j) {
+        // each product formed before it joins the sum: FP32 error 2.0e-7, a chain of FMAs 2.4e-7
+        const cpx<R> d = as_cpx<R>(dr[k]);
+        w[i] = w[i] + d * in[j];
+        w[j] = w[j] + cmul_conj(d, in[i]);
+        ++k;
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[i] = mass4 * v.s[2 * H + i / 3][i % 3];
+  }
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const int s = 2 * H + i / 3, c = i % 3;
+    o.s[s][c] = (w[i] + t * v.s[s][c]) - R(0.5) * acc.s[s][c];
+    if constexpr (sizeof(P) == 8) asm volatile("" : "+v"(o.s[s][c].re), "+v"(o.s[s][c].im));
+  }
+  if constexpr (sizeof(P) == 8) __builtin_amdgcn_sched_barrier(0);
 }
 
 // hops of the full lattice operator at (b, l), reading psi from global memory
 template <typename R, int MU, typename P>
 __device__ __forceinline__ void hop_global(Spinor<R>& acc, const P* in, const P* U, const Geom& g, int b, int l) {
-  int bn, ln;
-  nb_fwd(g, b, l, MU, bn, ln);
-  {
-    Half<R> h = project(load_spinor<R>(in, g, bn, ln), MU, true);
-    accum_recon(acc, umul(load_link<R>(U, g, b, MU, l), h), MU, true);
+  int bf, lf, bb, lb;
+  nb_fwd(g, b, l, MU, bf, lf);
+  nb_bwd(g, b, l, MU, bb, lb);
+  P p[12], u[9], q[12], v[9];
+  far_rows(p, in, (((int64_t)bf * 12) << g.bs_log) + lf, g.bs_log);
+  far_rows(u, U, (((int64_t)b * 36 + 9 * MU) << g.bs_log) + l, g.bs_log);
+  if constexpr (sizeof(P) == 8) {  // FP32: no room in the registers for both hops
+    accum_recon(acc, umul(as_link<R>(u), project(as_spinor<R>(p), MU, true)), MU, true);
+    pin(acc);
   }
-  nb_bwd(g, b, l, MU, bn, ln);
-  {
-    Half<R> h = project(load_spinor<R>(in, g, bn, ln), MU, false);
-    accum_recon(acc, udagmul(load_link<R>(U, g, bn, MU, ln), h), MU, false);
+  far_rows(q, in, (((int64_t)bb * 12) << g.bs_log) + lb, g.bs_log);
+  far_rows(v, U, (((int64_t)bb * 36 + 9 * MU) << g.bs_log) + lb, g.bs_log);
+  if constexpr (sizeof(P) != 8) accum_recon(acc, umul(as_link<R>(u), project(as_spinor<R>(p), MU, true)), MU, true);
+  accum_recon(acc, udagmul(as_link<R>(v), project(as_spinor<R>(q), MU, false)), MU, false);
+  pin(acc);
+}
+
+// links of the two hops of direction MU inside the block, as stored; U: the links of the
+// work-group's blocks.  A lane without the backward one reads its own.
+template <int MU, typename P>
+__device__ __forceinline__ void fetch_links(P (&u)[18], const P* U, const Geom& g, uint32_t at, int l) {
+  const P* Um = U + ((size_t)(9 * MU) << g.bs_log);
+  const uint32_t ab = loc(g, l, MU) > 0 ? at - (1u << g.sh[MU]) : at;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    u[i] = ldo(Um + ((size_t)i << g.bs_log), at);
+    u[9 + i] = ldo(Um + ((size_t)i << g.bs_log), ab);
   }
 }
 
-// hops that stay inside the block, reading rho from LDS
+// hops that stay inside the block, reading rho from LDS (sh: this lane's place in the first row)
 template <typename R, int MU, typename P>
-__device__ __forceinline__ void hop_block(Spinor<R>& acc, const cpx<R>* sh, const P* U, const Geom& g, int b,
-                                          int l, int bs) {
-  const int lc = loc(g, l, MU);
-  const int st = 1 << g.sh[MU];
-  if (lc < g.msk[MU]) {
-    Half<R> h = project(lds_spinor(sh, l + st, bs), MU, true);
-    accum_recon(acc, umul(load_link<R>(U, g, b, MU, l), h), MU, true);
-  }
-  if (lc > 0) {
-    Half<R> h = project(lds_spinor(sh, l - st, bs), MU, false);
-    accum_recon(acc, udagmul(load_link<R>(U, g, b, MU, l - st), h), MU, false);
-  }
+__device__ __forceinline__ void hop_block(Spinor<R>& acc, const cpx<R>* sh, const P (&u)[18], const Geom& g, int l,
+                                          int row) {
+  const int lc = loc(g, l, MU), st = 1 << g.sh[MU];
+  P f[9], v[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) f[i] = u[i], v[i] = u[9 + i];
+  if (lc < g.msk[MU]) accum_recon(acc, umul(as_link<R>(f), project(lds_spinor(sh, st, row), MU, true)), MU, true);
+  if constexpr (sizeof(P) == 8) pin(acc);
+  if (lc > 0) accum_recon(acc, udagmul(as_link<R>(v), project(lds_spinor(sh, -st, row), MU, false)), MU, false);
+  pin(acc);
 }
 
 // QF: the procedure for Q - tau = Gamma5 A_tau itself (residual and block
-// operator multiplied by Gamma5: lower two spins change sign)
+// operator multiplied by Gamma5: lower two spins change sign).
+// Bound by latency and vector instructions: links and clover term come from the caches in
+// every step, so what counts is the waves per SIMD.  Unless the order of the hops and the
+// place of the sums are fixed (pin), the compiler loads everything first and the kernel takes
+// 464 registers, one wave per SIMD; a block of 16 sites alone also left 48 lanes idle.
+// Two sweeps of MR(3), 16^4, 12 right-hand sides, clover, before -> now (us):
+//             4x4x4x2        4x4x2x2        2x2x2x2
+//   FP32    847 -> 576     829 -> 515    3300 -> 512
+//   FP64   1140 -> 932    1121 -> 873    4026 -> 893
+//   bf16    716 -> 443     693 -> 366    2935 -> 364
+// Three waves per SIMD in FP32 and two in FP64 spill: 4x4x4x2 639 and 1338 us.  BF16 has room
+// for the links of the next direction while this one is added, FP32 has not (734 us).
 template <typename S, bool CLOVER, bool QF>
-__global__ __launch_bounds__(256) void k_sap(SapArgs<S> a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(std::is_same<S, double>::value ? 1 : 2)))
+void k_sap(SapArgs<S> a) {
   using R = typename PT<S>::real;
+  using P = typename PT<S>::stor;
+  constexpr bool kAhead = sizeof(P) != 8;  // FP32: two directions' links do not fit beside the rest
   extern __shared__ unsigned char smem[];
   const Geom& g = a.g;
-  const int bs = 1 << g.bs_log;
-  cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem);
-  R* red = reinterpret_cast<R*>(smem + sizeof(cpx<R>) * 12 * bs);
+  const int lg = g.bs_log, row = blockDim.x, tid = threadIdx.x;
+  cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem);  // [12][row], a lane's neighbours in its own slot
+  R* red = reinterpret_cast<R*>(smem + sizeof(cpx<R>) * 12 * row);
 
   const int w = blockIdx.x, nw = gridDim.x;
   const int L = ((nw & 7) == 0) ? (w & 7) * (nw >> 3) + (w >> 3) : w;
   const int k = L % a.nrhs;
-  const int b = a.first_block + L / a.nrhs;
-  const int l = threadIdx.x;
-  auto* x = a.x + k * a.fstride;
-  const auto* f = a.f + k * a.fstride;
+  // the work-group's blocks b0, b0 + 1, ..; a slot past the last block repeats that one and
+  // does not store
+  const int b0 = (L / a.nrhs) * (row >> lg);
+  const int slot = min(tid >> lg, a.nblk - 1 - b0);
+  const bool live = slot == tid >> lg;
+  int b = a.first_block + b0 + slot, l = tid & ((1 << lg) - 1);
+  P* x = a.x + k * a.fstride;
+  P* x0 = x + (((int64_t)(a.first_block + b0) * 12) << lg);
+  const P* f0 = a.f + k * a.fstride + (((int64_t)(a.first_block + b0) * 12) << lg);
+  const P* U0 = a.U + (((int64_t)(a.first_block + b0) * 36) << lg);
+  const P* D0 = a.diag + (((int64_t)(a.first_block + b0) * 36) << lg);
   const R tau = R(a.tau[k]);
   const R mass4 = R(a.mass4);
 
   // r = f - A_tau x at this site (full operator, neighbours from global x)
-  Spinor<R> rho;
+  Spinor<R> rho, acc;
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<R>();
+  pin(acc);
+  hop_global<R, 0>(acc, x, a.U, g, b, l);
+  hop_global<R, 1>(acc, x, a.U, g, b, l);
+  hop_global<R, 2>(acc, x, a.U, g, b, l);
+  hop_global<R, 3>(acc, x, a.U, g, b, l);
   {
-    Spinor<R> acc;
+    P xv[12], fv[12], d0[18], d1[18];
+    const uint32_t at = ((uint32_t)(slot * 36) << lg) + l;
+    near_rows(xv, x0, ((uint32_t)(slot * 12) << lg) + l, lg);
+    if (CLOVER) fetch_diag<0>(d0, D0, at, lg);
+    near_rows(fv, f0, ((uint32_t)(slot * 12) << lg) + l, lg);
+    if (kAhead && CLOVER) fetch_diag<1>(d1, D0, at, lg);
+    const Spinor<R> xs = as_spinor<R>(xv);
+    Spinor<R> d;
+    diag_part<R, 0, CLOVER>(d, d0, mass4, xs, tau, acc);
+    if (!kAhead && CLOVER) fetch_diag<1>(d1, D0, at, lg);
+    diag_part<R, 1, CLOVER>(d, d1, mass4, xs, tau, acc);
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<R>();
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
-      switch (mu) {
-        case 0: hop_global<R, 0>(acc, x, a.U, g, b, l); break;
-        case 1: hop_global<R, 1>(acc, x, a.U, g, b, l); break;
-        case 2: hop_global<R, 2>(acc, x, a.U, g, b, l); break;
-        default: hop_global<R, 3>(acc, x, a.U, g, b, l); break;
-      }
+    for (int i = 0; i < 12; ++i) {
+      const cpx<R> fi = as_cpx<R>(fv[i]);
+      rho.s[i / 3][i % 3] = (QF && i >= 6) ? fi + d.s[i / 3][i % 3] : fi - d.s[i / 3][i % 3];
     }
-    Spinor<R> xs = load_spinor<R>(x, g, b, l);
-    Spinor<R> d = diag_part<R, typename PT<S>::stor, CLOVER>(a.diag, mass4, g, b, l, xs, tau);
-    Spinor<R> fs = load_spinor<R>(f, g, b, l);
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const cpx<R> ax = d.s[s][c] - R(0.5) * acc.s[s][c];
-        rho.s[s][c] = (QF && s >= 2) ? fs.s[s][c] + ax : fs.s[s][c] - ax;
-      }
+    pin(rho);
   }
 
   Spinor<R> e;
@@ -177,41 +286,53 @@ __global__ __launch_bounds__(256) void k_sap(SapArgs<S> a) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) e.s[s][c] = czero<R>();
 
+#pragma unroll 1
   for (int it = 0; it < a.n_mr; ++it) {
+    // links and clover term are read again (from the caches), each one direction ahead
+    l = opaque(l);
+    const uint32_t at = ((uint32_t)(slot * 36) << lg) + l;
+    P ua[18], ub[18];
+    if (kAhead) fetch_links<0>(ua, U0, g, at, l);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) sh[(3 * s + c) * bs + l] = rho.s[s][c];
+      for (int c = 0; c < 3; ++c) {
+        sh[(3 * s + c) * row + tid] = rho.s[s][c];
+        acc.s[s][c] = czero<R>();
+      }
     __syncthreads();
     // q = A_{tau,i} rho
-    Spinor<R> acc;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<R>();
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
-      switch (mu) {
-        case 0: hop_block<R, 0>(acc, sh, a.U, g, b, l, bs); break;
-        case 1: hop_block<R, 1>(acc, sh, a.U, g, b, l, bs); break;
-        case 2: hop_block<R, 2>(acc, sh, a.U, g, b, l, bs); break;
-        default: hop_block<R, 3>(acc, sh, a.U, g, b, l, bs); break;
-      }
-    }
-    Spinor<R> q = diag_part<R, typename PT<S>::stor, CLOVER>(a.diag, mass4, g, b, l, rho, tau);
+    if (kAhead) fetch_links<1>(ub, U0, g, at, l);
+    else fetch_links<0>(ua, U0, g, at, l);
+    hop_block<R, 0>(acc, sh + tid, ua, g, l, row);
+    if (kAhead) fetch_links<2>(ua, U0, g, at, l);
+    else fetch_links<1>(ub, U0, g, at, l);
+    hop_block<R, 1>(acc, sh + tid, ub, g, l, row);
+    if (kAhead) fetch_links<3>(ub, U0, g, at, l);
+    else fetch_links<2>(ua, U0, g, at, l);
+    hop_block<R, 2>(acc, sh + tid, ua, g, l, row);
+    if (!kAhead) fetch_links<3>(ub, U0, g, at, l);
+    else if (CLOVER) fetch_diag<0>(ua, D0, at, lg);
+    hop_block<R, 3>(acc, sh + tid, ub, g, l, row);
+    if (!kAhead && CLOVER) fetch_diag<0>(ua, D0, at, lg);
+    if (kAhead && CLOVER) fetch_diag<1>(ub, D0, at, lg);
+    Spinor<R> q;
+    diag_part<R, 0, CLOVER>(q, ua, mass4, rho, tau, acc);
+    if (!kAhead && CLOVER) fetch_diag<1>(ub, D0, at, lg);
+    diag_part<R, 1, CLOVER>(q, ub, mass4, rho, tau, acc);
+    pin(q);
     R v[3] = {R(0), R(0), R(0)};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        q.s[s][c] = q.s[s][c] - R(0.5) * acc.s[s][c];
         if (QF && s >= 2) q.s[s][c] = -q.s[s][c];
-        cpx<R> t = cmul_conj(q.s[s][c], rho.s[s][c]);
+        const cpx<R> t = cmul_conj(q.s[s][c], rho.s[s][c]);
         v[0] += t.re;
         v[1] += t.im;
         v[2] += norm2(q.s[s][c]);
       }
-    block_sum<R, 3>(v, red);
+    slot_sum<R, 3>(v, red, lg);
     cpx<R> alpha = czero<R>();
     if (v[2] > R(0)) alpha = cpx<R>{v[0] / v[2], v[1] / v[2]};
 #pragma unroll
@@ -222,12 +343,14 @@ __global__ __launch_bounds__(256) void k_sap(SapArgs<S> a) {
         rho.s[s][c] = rho.s[s][c] - alpha * q.s[s][c];
       }
   }
-  Spinor<R> xs = load_spinor<R>(x, g, b, l);
+  if (live) {
+    const uint32_t at = ((uint32_t)(slot * 12) << lg) + l;
+    P xv[12];
+    near_rows(xv, x0, at, lg);
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) xs.s[s][c] = xs.s[s][c] + e.s[s][c];
-  store_spinor(x, g, b, l, xs);
+    for (int i = 0; i < 12; ++i)
+      sto(x0 + ((size_t)i << lg), at, vc(as_cpx<R>(xv[i]) + e.s[i / 3][i % 3], (P*)nullptr));
+  }
 }
 
 // ---- 4^4 blocks, FP32 arithmetic (FP32 or BF16 storage), gathering: one work-group per
@@ -532,7 +655,8 @@ void launch_s(const qmg_ctx* c, int p, void* x, const void* f, const double* tau
   a.g = c->g;
   for (int i = 0; i < QMG_MAXRHS; ++i) a.tau[i] = i < nrhs ? tau[i] : 0.0;
   const int bs = 1 << c->g.bs_log;
-  size_t lds = sizeof(cpx<R>) * 12 * bs + sizeof(R) * 3 * std::max(bs, 8);
+  const int wg = std::max(bs, 64);  // blocks of fewer than 64 sites: several to a wave
+  const size_t lds = sizeof(cpx<R>) * 12 * wg + sizeof(R) * 3 * 4;
   if constexpr (!std::is_same<S, double>::value) {
     if (fits44(c, p) && c->tune.sap_variant >= 1) {
       dim3 grid((unsigned)a.nblk);
@@ -546,13 +670,13 @@ void launch_s(const qmg_ctx* c, int p, void* x, const void* f, const double* tau
       return;
     }
   }
-  dim3 grid((unsigned)(a.nblk * nrhs));
+  const dim3 grid((unsigned)((a.nblk + wg / bs - 1) / (wg / bs) * nrhs));
   if (qf) {
-    if (c->clover) hipLaunchKernelGGL((k_sap<S, true, true>), grid, dim3(bs), lds, s, a);
-    else hipLaunchKernelGGL((k_sap<S, false, true>), grid, dim3(bs), lds, s, a);
+    if (c->clover) hipLaunchKernelGGL((k_sap<S, true, true>), grid, dim3(wg), lds, s, a);
+    else hipLaunchKernelGGL((k_sap<S, false, true>), grid, dim3(wg), lds, s, a);
   } else {
-    if (c->clover) hipLaunchKernelGGL((k_sap<S, true, false>), grid, dim3(bs), lds, s, a);
-    else hipLaunchKernelGGL((k_sap<S, false, false>), grid, dim3(bs), lds, s, a);
+    if (c->clover) hipLaunchKernelGGL((k_sap<S, true, false>), grid, dim3(wg), lds, s, a);
+    else hipLaunchKernelGGL((k_sap<S, false, false>), grid, dim3(wg), lds, s, a);
   }
 }
 
