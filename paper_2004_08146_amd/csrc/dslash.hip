@@ -32,9 +32,39 @@ struct DsArgs {
   double tau[QMG_MAXRHS];
 };
 
-// acc += (I - g_mu) U_mu(x) psi(x+mu) + (I + g_mu) U_mu(x-mu)^H psi(x-mu)
+// the values are formed here: left to itself the compiler defers a direction's sums to the
+// end and keeps their terms in registers instead
+template <typename C>
+__device__ __forceinline__ void pin(Spinor<C>& p) {
+#pragma unroll
+  for (int i = 0; i < 12; ++i) asm volatile("" : "+v"(p.s[i / 3][i % 3].re), "+v"(p.s[i / 3][i % 3].im));
+}
+
+// N rows of 1 << lg elements from element `at` on
+template <typename R, int N, typename P>
+__device__ __forceinline__ void rows(cpx<R> (&v)[N], const P* f, int64_t at, int lg) {
+  const P* q = f + at;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = ldcv<R>(q, (int64_t)i << lg);
+}
+template <typename R>
+__device__ __forceinline__ Half<R> project_rows(const cpx<R> (&v)[12], int mu, bool fwd) {
+  Spinor<R> p;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) p.s[i / 3][i % 3] = v[i];
+  return project(p, mu, fwd);
+}
+template <typename R>
+__device__ __forceinline__ Link<R> link_rows(const cpx<R> (&v)[9]) {
+  Link<R> u;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) u.u[i / 3][i % 3] = v[i];
+  return u;
+}
+
+// hop_pair below with the order of loads and sums left to the compiler
 template <typename R, int MU, typename PI, typename P>
-__device__ __forceinline__ void hop_pair(Spinor<R>& acc, const PI* in, const P* U, const Geom& g, int b, int l) {
+__device__ __forceinline__ void hop_pair_free(Spinor<R>& acc, const PI* in, const P* U, const Geom& g, int b, int l) {
   int bn, ln;
   nb_fwd(g, b, l, MU, bn, ln);
   {
@@ -48,8 +78,32 @@ __device__ __forceinline__ void hop_pair(Spinor<R>& acc, const PI* in, const P* 
   }
 }
 
-template <typename S, bool CLOVER, int MODE, bool UB, typename SI>
-__global__ __launch_bounds__(256) void k_dslash(DsArgs<S, SI> a) {
+// acc += (I - g_mu) U_mu(x) psi(x+mu) + (I + g_mu) U_mu(x-mu)^H psi(x-mu)
+template <typename R, int MU, typename PI, typename P>
+__device__ __forceinline__ void hop_pair(Spinor<R>& acc, const PI* in, const P* U, const Geom& g, int b, int l) {
+  const int lg = g.bs_log;
+  int bn, ln;
+  cpx<R> p[12], u[9], q[12], v[9];
+  nb_fwd(g, b, l, MU, bn, ln);
+  rows(p, in, (((int64_t)bn * 12) << lg) + ln, lg);
+  rows(u, U, (((int64_t)b * 36 + 9 * MU) << lg) + l, lg);
+  nb_bwd(g, b, l, MU, bn, ln);
+  rows(q, in, (((int64_t)bn * 12) << lg) + ln, lg);
+  rows(v, U, (((int64_t)bn * 36 + 9 * MU) << lg) + ln, lg);
+  accum_recon(acc, umul(link_rows(u), project_rows(p, MU, true)), MU, true);
+  accum_recon(acc, udagmul(link_rows(v), project_rows(q, MU, false)), MU, false);
+  // FP64: two directions ahead
+  if constexpr (sizeof(R) == 4 || MU % 2 == 1) pin(acc);
+  if constexpr (sizeof(R) == 4) __builtin_amdgcn_sched_barrier(0);
+}
+
+// General blocks.  Bound by the loads of 8 neighbours, whose lines other work-groups share
+// through the caches: what counts is how many are in flight.  FREE: the compiler orders loads
+// and sums, loads nearly all first and takes 256-330 registers; else one direction (FP64: two)
+// at a time, which leaves room for more waves.  The choice is made in launch_t.
+template <typename S, bool CLOVER, int MODE, bool UB, typename SI, bool FREE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FREE || std::is_same<S, double>::value ? 1 : 2)))
+void k_dslash(DsArgs<S, SI> a) {
   using R = typename PT<S>::real;
   const Geom& g = a.g;
   const int w = blockIdx.x, nw = gridDim.x;
@@ -69,15 +123,21 @@ __global__ __launch_bounds__(256) void k_dslash(DsArgs<S, SI> a) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<R>();
 
-  // one direction at a time keeps a single neighbour in flight per thread
+  if constexpr (FREE) {
 #pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    switch (mu) {
-      case 0: hop_pair<R, 0>(acc, in, a.U, g, b, l); break;
-      case 1: hop_pair<R, 1>(acc, in, a.U, g, b, l); break;
-      case 2: hop_pair<R, 2>(acc, in, a.U, g, b, l); break;
-      default: hop_pair<R, 3>(acc, in, a.U, g, b, l); break;
+    for (int mu = 0; mu < 4; ++mu) {
+      switch (mu) {
+        case 0: hop_pair_free<R, 0>(acc, in, a.U, g, b, l); break;
+        case 1: hop_pair_free<R, 1>(acc, in, a.U, g, b, l); break;
+        case 2: hop_pair_free<R, 2>(acc, in, a.U, g, b, l); break;
+        default: hop_pair_free<R, 3>(acc, in, a.U, g, b, l); break;
+      }
     }
+  } else {
+    hop_pair<R, 0>(acc, in, a.U, g, b, l);
+    hop_pair<R, 1>(acc, in, a.U, g, b, l);
+    hop_pair<R, 2>(acc, in, a.U, g, b, l);
+    hop_pair<R, 3>(acc, in, a.U, g, b, l);
   }
   const Spinor<R> self = load_spinor<R>(in, g, b, l);
   Spinor<R> o;
@@ -201,14 +261,6 @@ __device__ __forceinline__ void l44_face(Half<C>& fh, Half<C>& fw, const PI* in,
   const Spinor<C> pb = ld_spinor44<C>(in, (uint32_t)nbr[b * 8 + 2 * MU + 1], l44_site<MU>(j, 3));
   fh = project(pf, MU, true);
   fw = udagmul(u, project(pb, MU, false));
-}
-
-// the values are formed here: left to itself the compiler defers a direction's sums to the
-// end and keeps their terms in registers instead
-template <typename C>
-__device__ __forceinline__ void pin(Spinor<C>& p) {
-#pragma unroll
-  for (int i = 0; i < 12; ++i) asm volatile("" : "+v"(p.s[i / 3][i % 3].re), "+v"(p.s[i / 3][i % 3].im));
 }
 
 template <typename C, int MU, bool TWO>
@@ -486,10 +538,28 @@ void launch_t(const qmg_ctx* c, void* out, const void* in, const double* tau, in
   }
   const int wg = 256;
   unsigned nwg = (unsigned)((c->g.V + wg - 1) / wg) * (unsigned)nrhs;
-  if ((1 << c->g.bs_log) >= wg)
-    hipLaunchKernelGGL((k_dslash<S, CLOVER, MODE, true, SI>), dim3(nwg), dim3(wg), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_dslash<S, CLOVER, MODE, false, SI>), dim3(nwg), dim3(wg), 0, s, a);
+  auto go = [&](auto ub, auto free) {
+    hipLaunchKernelGGL((k_dslash<S, CLOVER, MODE, decltype(ub)::value, SI, decltype(free)::value>), dim3(nwg), dim3(wg),
+                       0, s, a);
+  };
+  // FREE (all loads early, one or two waves per SIMD) against the fixed order (more waves, less
+  // in flight in each): it is the better one where the links are not read again for further
+  // right-hand sides or there are too few waves anyway, and where the block, and so every
+  // address, is uniform.  FP32, blocks 4x4x4x2: 32x32x16x16, 1 rhs 56.7 against 61.0 us, 3 rhs
+  // 162 / 124; 16x8^3, 4 rhs 11.6 / 12.0; 16^4, 2 rhs 26.9 / 21.6, 12 rhs 145 / 108.  Blocks
+  // 8x4x4x2, 32x32x16x16, 3 rhs: FP32 121 / 130, FP64 241 / 277, bf16 73 / 60 (1 rhs, 32^3x16:
+  // 55.5 / 60.2).  Blocks 4x4x4x2, 16^4, 12 rhs: FP64 228 / 211, bf16 169 / 59; 1 rhs 32x16^3:
+  // FP64 59.1 / 57.8, bf16 31.8 / 16.7.
+  constexpr bool kF32 = std::is_same<S, float>::value, kBf16 = std::is_same<S, bf16_t>::value;
+  if ((1 << c->g.bs_log) >= wg) {
+    if constexpr (kBf16)
+      if (nrhs > 1) return go(std::true_type{}, std::false_type{});
+    go(std::true_type{}, std::true_type{});
+  } else {
+    if constexpr (kF32)
+      if (nrhs == 1 || nwg <= 256) return go(std::false_type{}, std::true_type{});
+    go(std::false_type{}, std::false_type{});
+  }
 }
 
 template <typename S>
