@@ -34,11 +34,12 @@ FP32_NONPACKED_TFLOPS = 78.6
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic_64x32x32x32_16rhs.json")
 # sources that define each profiled kernel: a change to any of them voids its counters
 KERNEL_SOURCES = {
-    "sap_f32": ["paper_2004_08146_amd/csrc/sap.hip", "paper_2004_08146_amd/csrc/qmg_device.h"],
+    "sap_f32": ["paper_2004_08146_amd/csrc/sap44.hip", "paper_2004_08146_amd/csrc/sap.hip",
+                "paper_2004_08146_amd/csrc/qmg_device.h"],
     "stencil_f32": ["paper_2004_08146_amd/csrc/dslash.hip", "paper_2004_08146_amd/csrc/qmg_device.h",
                     "paper_2004_08146_amd/csrc/tune.hip"],
 }
-KERNEL_NAMES = {"sap_f32": "k_sap44<float, true, 2, false>", "stencil_f32": "k_dslash"}
+KERNEL_NAMES = {"sap_f32": "k_sap44h<float, true, false>", "stencil_f32": "k_dslash"}
 
 
 def sap_flops_per_site(n_mr):
@@ -203,15 +204,18 @@ def summarize_pmc(fetch_dir, write_dir, cmd):
                    "kernel: after the autotuner), HBM bytes = 1024 * (FETCH_SIZE * fetch_factor + "
                    "WRITE_SIZE * write_factor)",
            "kernels": {}}
-    # the kernels mode runs, after the autotuner: f64 1-rhs apply x4, f32 16-rhs apply x4, SAP sweep x3 (6 launches)
+    # the kernels mode runs, after the autotuner: f64 1-rhs apply x4, f32 16-rhs apply x4, SAP sweep x3 (each the
+    # halo of one colour's x, then two half-sweeps; the half-sweeps are the ones averaged)
     picks = {"stencil_f32": (lambda n: short(n).startswith("k_dslash") and "float" in short(n)
                              and "double" not in short(n), 4),
-             "sap_f32": (lambda n: short(n) == KERNEL_NAMES["sap_f32"], 6)}
+             "sap_f32": (lambda n: short(n) == KERNEL_NAMES["sap_f32"], 9)}
     for key, (match, last) in picks.items():
         fsel = [(i, n, v) for i, n, v in fet if match(n)][-last:]
         wsel = [(i, n, v) for i, n, v in wri if match(n)][-last:]
         if not fsel or not wsel:
             continue
+        if key == "sap_f32":
+            fsel, wsel = ([d for j, d in enumerate(v) if j % 3] for v in (fsel, wsel))
         f_kib, w_kib = float(np.mean([v for _, _, v in fsel])), float(np.mean([v for _, _, v in wsel]))
         out["kernels"][key] = {"kernel": short(fsel[-1][1]), "launches": len(fsel),
                                "fetch_kib": f_kib, "write_kib": w_kib,
@@ -704,15 +708,16 @@ def main():
         qapply["%s_%drhs" % (prec, n)] = {"ms": ms, "gflops": FLOP_SITE * V * n / ms / 1e6,
                                           "gbps": byts / ms / 1e6, "hbm_frac": byts / ms / 1e6 / HBM_PEAK_GBS}
     # SAP sweep (FP32, all rhs): the smoother inside every V-cycle and the
-    # dominant kernel of the solve; one sweep = two launches (one per colour)
+    # dominant kernel of the solve; one sweep = two launches (one per colour), after
+    # one that writes the halo of the initial x (its time is counted with them)
     xs = lat.field(nrhs, "f32")
     fs = lat.field(nrhs, "f32")
     sap_ms = timer(lambda: lat.sap_smooth(xs, fs, taus, nrhs, 1, 3, "f32"), 10)
     sap_bytes = sap_bytes_per_site("f32", nrhs, True) * V
     del xs, fs
     launch_ms = sap_ms / 2
-    # the dominant kernel of the solve (about 40% of its kernel time): one colour's SAP half-sweep
-    roofline = roofline_entry("k_sap44<float, clover, 2 rhs slots>: one colour's SAP half-sweep, 16 rhs",
+    # the dominant kernel of the solve (about 35% of its kernel time): one colour's SAP half-sweep
+    roofline = roofline_entry("k_sap44h<float, clover>: one colour's SAP half-sweep with its halo, 16 rhs",
                               sap_flops_per_site(3) * (V // 2) * nrhs, sap_bytes / 2, launch_ms,
                               FP32_VECTOR_PEAK_TFLOPS, traffic_for("sap_f32"))
     roofline["flop_per_site_rhs"] = sap_flops_per_site(3)
@@ -742,7 +747,7 @@ def main():
                        "achieved": cfl / cms / 1e9, "peak": MFMA_PEAK_TFLOPS["f32"], "unit": "TFLOP/s",
                        "frac": cfl / cms / 1e9 / MFMA_PEAK_TFLOPS["f32"], "launch_ms": cms,
                        "mfma_flop_per_launch": cfl,
-                       "mfma_util_pct": mfma_util_for("k_coarse_mfma<float, float, 3>")}
+                       "mfma_util_pct": mfma_util_for("k_coarse_mfma<float, 3, false>")}
 
     del lat
     torch.cuda.empty_cache()
