@@ -182,14 +182,17 @@ __global__ __launch_bounds__(256) void k_restrict(Geom g, typename PT<C>::stor* 
   const int ng = (nrhs + NR - 1) / NR;
   const int b = blockIdx.x / (2 * ng), q = blockIdx.x - b * 2 * ng, h = q & 1, k0 = (q >> 1) * NR;
   const int l = threadIdx.x, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const bool on = l < (1 << g.bs_log);  // blocks of fewer than 64 sites leave lanes idle
+  // blocks of fewer than 64 sites leave lanes idle: those load site 0 and add nothing (a load
+  // behind a branch waited for the one before in BF16: 256 blocks, ntv 24, 1 rhs 49 us, now 14)
+  const bool on = l < (1 << g.bs_log);
+  const int ls = on ? l : 0;
   const int nr = min(NR, nrhs - k0), nc = 2 * ntv;
   cpx<R> vv[NR][6];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
 #pragma unroll
     for (int d = 0; d < 6; ++d)
-      vv[r][d] = on && r < nr ? ldcv<R>(v + (int64_t)(k0 + r) * fstride, sidx(g, b, 6 * h + d, l)) : czero<R>();
+      vv[r][d] = ldcv<R>(v + (int64_t)(k0 + min(r, nr - 1)) * fstride, sidx(g, b, 6 * h + d, ls));
   int rb = 0;
   for (int j0 = 0; j0 < ntv; j0 += NJ) {
     double acc[NV];
@@ -199,14 +202,14 @@ __global__ __launch_bounds__(256) void k_restrict(Geom g, typename PT<C>::stor* 
       const int j = min(j0 + t, ntv - 1);
       cpx<R> p[6];
 #pragma unroll
-      for (int d = 0; d < 6; ++d) p[d] = on ? ldcv<R>(P, pidx(g, ntv, b, h, j, d, l)) : czero<R>();
+      for (int d = 0; d < 6; ++d) p[d] = ldcv<R>(P, pidx(g, ntv, b, h, j, d, ls));
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         cpx<R> s = czero<R>();
 #pragma unroll
         for (int d = 0; d < 6; ++d) cfma_conj(s, p[d], vv[r][d]);
-        acc[2 * (r * NJ + t)] = double(s.re);
-        acc[2 * (r * NJ + t) + 1] = double(s.im);
+        acc[2 * (r * NJ + t)] = on ? double(s.re) : 0.0;
+        acc[2 * (r * NJ + t) + 1] = on ? double(s.im) : 0.0;
       }
     }
     double* rd = red[rb];
