@@ -122,12 +122,13 @@ __global__ __launch_bounds__(kGmWG) void k_gm_coef(GmState st, const double* par
   const int J = j + 1, m = st.m, ld = J + (last ? 1 : 0);
   gm_sums(partial + (int64_t)k * ld * nchunk * 2, ld, nchunk, d);
   const double* sg = st.sig + (int64_t)k * (m + 1);
-  for (int i = threadIdx.x; i < J; i += kGmWG) {
-    const cpx<double> di = {d[i][0], d[i][1]};
-    stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * di);
-    if (!last) stz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j, (sg[i] * sg[j]) * di);
-  }
-  if (last && threadIdx.x == 0) {
+  if (!last) {
+    for (int i = threadIdx.x; i < J; i += kGmWG) {
+      const cpx<double> di = {d[i][0], d[i][1]};
+      stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * di);
+      stz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j, (sg[i] * sg[j]) * di);
+    }
+  } else if (threadIdx.x == 0) {  // scales d in place: no other thread reads it here
     double proj = 0.0;
     for (int i = 0; i < J; ++i) {
       const double s2 = sg[i] * sg[i];
