@@ -80,18 +80,21 @@ __global__ __launch_bounds__(kDotWG) void k_dot_stage1(double* partial, const ty
 
 // The loads of eight entries of one or two basis vectors are in flight together (8 coarse
 // vectors of 32^4, FP32, 10 basis vectors: 32 -> 23 us).
-// w_k += sum_j coef[k*J+j] V_j,k over one chunk, and partial[k][chunk] = ||new w_k||^2 there.
+// w_k = scale_k w_k + sum_j coef[k*J+j] V_j,k over one chunk, and partial[k][chunk] =
+// ||new w_k||^2 there; scale_k = basis_scale(sig[k*ldsig + aj]), or 1 without sig.
 // With a copy type C (FP32 or BF16 storage), the new w is also written to cp in
 // that storage, rounded through FP32 exactly as the conversion kernel rounds it.
 template <typename S, typename C = void>
 __global__ __launch_bounds__(kDotWG) void k_axpy_norm(typename PT<S>::stor* w, const typename PT<S>::stor* V,
-                                                     int64_t vstride, int J, const double* coef, int64_t n,
-                                                     int64_t stride, int nchunk, double* partial, C* cp) {
+                                                     int64_t vstride, int J, const double* coef, const double* sig,
+                                                     int ldsig, int aj, int64_t n, int64_t stride, int nchunk,
+                                                     double* partial, C* cp) {
   using R = typename PT<S>::real;
   __shared__ double red[2 * (kDotWG / 64)];
   const int chunk = blockIdx.x, k = blockIdx.y;
   const int64_t i0 = chunk * kChunk + threadIdx.x;
   auto* wk = w + k * stride;
+  const double al = sig ? basis_scale(sig[(int64_t)k * ldsig + aj]) : 1.0;
   double acc[2] = {0.0, 0.0};
   auto body = [&](auto fullc) {
     constexpr bool kFull = decltype(fullc)::value;
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kDotWG) void k_axpy_norm(typename PT<S>::stor* w, c
     };
     cpx<double> v[kDotPerThread];
 #pragma unroll
-    for (int t = 0; t < kDotPerThread; ++t) v[t] = get(wk, t);
+    for (int t = 0; t < kDotPerThread; ++t) v[t] = al * get(wk, t);
 #pragma unroll 2
     for (int j = 0; j < J; ++j) {
       const cpx<double> c = {coef[((int64_t)k * J + j) * 2], coef[((int64_t)k * J + j) * 2 + 1]};
@@ -149,11 +152,15 @@ __global__ __launch_bounds__(256) void k_dot_stage2(double* dots, const double* 
 }
 
 // As k_dot_stage2 for the projections of one Gram-Schmidt pass: dots as it, and for j < J
-// also the update's coefficients coef[k*J + j] = -sig_j^2 dots (basis v_j = sig_j W_j)
+// also the update's coefficients coef[k*J + j] = -scale sig_j^2 dots (basis v_j = sig_j W_j),
+// scale = basis_scale(sig_aj), or 1 for aj < 0
 __global__ __launch_bounds__(256) void k_project_stage2(double* dots, double* coef, const double* partial,
-                                                        const double* sig, int ldsig, int J, int JT, int nchunk) {
+                                                        const double* sig, int ldsig, int aj, int J, int JT,
+                                                        int nchunk) {
   __shared__ double red[2 * 4];
   const int j = blockIdx.x, k = blockIdx.y;
+  const double* sg = sig + (int64_t)k * ldsig;
+  const double s = sg[min(j, J - 1)], scale = aj < 0 ? 1.0 : basis_scale(sg[aj]);  // before the sums, not after
   const double* p = partial + ((int64_t)k * JT + j) * nchunk * 2;
   double acc[2] = {0.0, 0.0};
   for (int c = threadIdx.x; c < nchunk; c += blockDim.x) {
@@ -165,25 +172,27 @@ __global__ __launch_bounds__(256) void k_project_stage2(double* dots, double* co
     dots[((int64_t)k * JT + j) * 2] = acc[0];
     dots[((int64_t)k * JT + j) * 2 + 1] = acc[1];
     if (j < J) {
-      const double s = sig[(int64_t)k * ldsig + j], s2 = -s * s;
+      const double s2 = -s * s * scale;
       coef[((int64_t)k * J + j) * 2] = s2 * acc[0];
       coef[((int64_t)k * J + j) * 2 + 1] = s2 * acc[1];
     }
   }
 }
 
-// norms[2k] = ||w_k||^2 and the scale of w_k as basis vector `at`: sig = 1 / ||w_k||
+// norms[2k] = ||w_k||^2, norms[2k + 1] = basis_scale(sig_aj) (1 for aj < 0), and the scale of
+// w_k as basis vector `at`: sig = 1 / ||w_k||
 __global__ __launch_bounds__(256) void k_norm_stage2(double* norms, const double* partial, double* sig, int ldsig,
-                                                     int at, int nchunk) {
+                                                     int aj, int at, int nchunk) {
   __shared__ double red[2 * 4];
   const int k = blockIdx.x;
+  const double scale = aj < 0 ? 1.0 : basis_scale(sig[(int64_t)k * ldsig + aj]);
   const double* p = partial + (int64_t)k * nchunk * 2;
   double acc[2] = {0.0, 0.0};
   for (int c = threadIdx.x; c < nchunk; c += blockDim.x) acc[0] += p[2 * c];
   wg_sum<double, 2>(acc, red);
   if (threadIdx.x == 0) {
     norms[2 * k] = acc[0];
-    norms[2 * k + 1] = 0.0;
+    norms[2 * k + 1] = scale;
     const double h = sqrt(fmax(acc[0], 0.0));
     sig[(int64_t)k * ldsig + at] = h > 0.0 && isfinite(h) ? 1.0 / h : 0.0;
   }
@@ -192,6 +201,12 @@ __global__ __launch_bounds__(256) void k_norm_stage2(double* norms, const double
 __global__ void k_sig_init(double* sig, int ldsig, int nrhs) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < ldsig * nrhs) sig[i] = i % ldsig == 0 ? 1.0 : 0.0;
+}
+
+// sig_at = 0 for the right-hand sides in mask
+__global__ void k_sig_drop(double* sig, int ldsig, int at, uint64_t mask, int nrhs) {
+  const int k = threadIdx.x;
+  if (k < nrhs && (mask >> k & 1)) sig[(int64_t)k * ldsig + at] = 0.0;
 }
 
 template <typename S, typename SV = S>
@@ -314,24 +329,25 @@ hipError_t launch_multidot_shared(int p, double* dots, const void* V, int64_t vs
   return hipGetLastError();
 }
 
-// w_k += sum_j coef V_j,k; partial[k][chunk] = ||w_k||^2 over the chunk afterwards
+// w_k = scale_k w_k + sum_j coef V_j,k; partial[k][chunk] = ||w_k||^2 over the chunk afterwards
 hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
-                                int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy, int copy_prec) {
+                                int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy, int copy_prec,
+                                const double* sig, int ldsig, int aj) {
   const int nchunk = dot_chunks(n);
   const dim3 grid(nchunk, nrhs), blk(kDotWG);
   if (copy && p == QMG_F64 && copy_prec == QMG_F32) {
     hipLaunchKernelGGL((k_axpy_norm<double, float2>), grid, blk, 0, s, (double2*)w, (const double2*)V, vstride, J,
-                       coef, n, stride, nchunk, partial, (float2*)copy);
+                       coef, sig, ldsig, aj, n, stride, nchunk, partial, (float2*)copy);
   } else if (copy && p == QMG_F64 && copy_prec == QMG_BF16) {
     hipLaunchKernelGGL((k_axpy_norm<double, uint32_t>), grid, blk, 0, s, (double2*)w, (const double2*)V, vstride, J,
-                       coef, n, stride, nchunk, partial, (uint32_t*)copy);
+                       coef, sig, ldsig, aj, n, stride, nchunk, partial, (uint32_t*)copy);
   } else {
     if (copy) return hipErrorInvalidValue;  // only FP64 vectors are copied to FP32 / BF16
     by_prec(p, [&](auto tag) {
       using S = decltype(tag);
       using P = typename PT<S>::stor;
-      hipLaunchKernelGGL((k_axpy_norm<S, void>), grid, blk, 0, s, (P*)w, (const P*)V, vstride, J, coef, n, stride,
-                         nchunk, partial, (void*)nullptr);
+      hipLaunchKernelGGL((k_axpy_norm<S, void>), grid, blk, 0, s, (P*)w, (const P*)V, vstride, J, coef, sig, ldsig,
+                         aj, n, stride, nchunk, partial, (void*)nullptr);
     });
   }
   return hipGetLastError();
@@ -349,20 +365,27 @@ hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int 
 
 hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
                           int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
-                          hipStream_t s, int with_self) {
+                          hipStream_t s, int with_self, int aj) {
   const hipError_t e = launch_dot_partials(p, V, vstride, J, w, n, stride, nrhs, partial, s, with_self);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_project_stage2, dim3(J + with_self, nrhs), dim3(256), 0, s, dots, coef, partial, sig, ldsig, J,
-                     J + with_self, dot_chunks(n));
+  hipLaunchKernelGGL(k_project_stage2, dim3(J + with_self, nrhs), dim3(256), 0, s, dots, coef, partial, sig, ldsig, aj,
+                     J, J + with_self, dot_chunks(n));
   return hipGetLastError();
 }
 
 hipError_t launch_axpy_sig(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
-                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int at, double* partial,
-                           hipStream_t s, void* copy, int copy_prec) {
-  const hipError_t e = launch_axpy_partials(p, w, V, vstride, J, coef, n, stride, nrhs, partial, s, copy, copy_prec);
+                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int aj, int at,
+                           double* partial, hipStream_t s, void* copy, int copy_prec) {
+  const hipError_t e = launch_axpy_partials(p, w, V, vstride, J, coef, n, stride, nrhs, partial, s, copy, copy_prec,
+                                            aj < 0 ? nullptr : sig, ldsig, aj);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_norm_stage2, dim3(nrhs), dim3(256), 0, s, norms, partial, sig, ldsig, at, dot_chunks(n));
+  hipLaunchKernelGGL(k_norm_stage2, dim3(nrhs), dim3(256), 0, s, norms, partial, sig, ldsig, aj, at, dot_chunks(n));
+  return hipGetLastError();
+}
+
+hipError_t launch_sig_drop(double* sig, int ldsig, int at, uint64_t mask, int nrhs, hipStream_t s) {
+  static_assert(QMG_MAXRHS <= 64, "one bit per right-hand side");
+  hipLaunchKernelGGL(k_sig_drop, dim3(1), dim3(64), 0, s, sig, ldsig, at, mask, nrhs);
   return hipGetLastError();
 }
 

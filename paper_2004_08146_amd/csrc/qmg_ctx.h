@@ -166,10 +166,11 @@ hipError_t launch_multidot(int p, double* dots, const void* V, int64_t vstride, 
 int dot_chunks(int64_t n);
 hipError_t launch_dot_partials(int p, const void* V, int64_t vstride, int J, const void* w, int64_t n, int64_t stride,
                                int nrhs, double* partial, hipStream_t s, int with_self = 0);
-// the update and the chunk sums of its squared norm: partial[(k*dot_chunks(n) + chunk)*2 ..]
+// the update and the chunk sums of its squared norm: partial[(k*dot_chunks(n) + chunk)*2 ..];
+// with sig ([nrhs][ldsig] on the device) w is first scaled by the power of two below sig_aj (0 for 0)
 hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                                 int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy = nullptr,
-                                int copy_prec = QMG_F64);
+                                int copy_prec = QMG_F64, const double* sig = nullptr, int ldsig = 0, int aj = 0);
 // w_k += sum_j coef[k*J + j] V_j,k and norms[2k] = ||w_k||^2 of the result; with copy
 // (p == QMG_F64 only) the result is also written there in copy_prec (FP32 or BF16),
 // bit for bit what launch_convert would write
@@ -177,16 +178,19 @@ hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int 
                             int64_t stride, int nrhs, double* norms, double* partial, hipStream_t s,
                             void* copy = nullptr, int copy_prec = QMG_F64);
 // One Gram-Schmidt pass on a basis v_j = sig_j W_j (sig: [nrhs][ldsig] on the device): the
-// projections dots (as launch_multidot) with the update's coefficients -sig_j^2 dots, and
-// the update with the squared norms of its results and their scales as basis vector `at`
+// projections dots (as launch_multidot) with the update's coefficients -scale sig_j^2 dots, and
+// the update of scale w with (squared norm, scale) of its results in norms and their sig as
+// basis vector `at`; scale: the power of two below sig_aj (0 for 0), 1 for aj < 0
 hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
                           int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
-                          hipStream_t s, int with_self);
+                          hipStream_t s, int with_self, int aj);
 hipError_t launch_axpy_sig(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
-                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int at, double* partial,
-                           hipStream_t s, void* copy = nullptr, int copy_prec = QMG_F64);
+                           int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int aj, int at,
+                           double* partial, hipStream_t s, void* copy = nullptr, int copy_prec = QMG_F64);
 // sig = (1, 0, 0, ...) for every right-hand side
 hipError_t launch_sig_init(double* sig, int ldsig, int nrhs, hipStream_t s);
+// sig_at = 0 for the right-hand sides whose bit is set in mask
+hipError_t launch_sig_drop(double* sig, int ldsig, int at, uint64_t mask, int nrhs, hipStream_t s);
 // w_k += sum_j coef[k*J + j] * V_j,k   (coef complex double on device)
 hipError_t launch_multiaxpy(int p, void* w, const void* V, int64_t vstride, int J, const double* coef,
                             int64_t n, int64_t stride, int nrhs, hipStream_t s);

@@ -357,6 +357,14 @@ QMG_HD Spinor<R> apply_diag(const P* D, const Geom& g, int b, int l, const Spino
   return o;
 }
 
+// The scale that the update of a Gram-Schmidt step takes from the last basis vector's
+// sig = 1 / ||W_j||: the power of two below it, so that ||W_{j+1}|| stays near h_{j+1,j}
+// = ||A v_j - projections|| instead of becoming the product of all of them, and no digit
+// changes.  0 for a vector that is zero or dropped (sig = 0): what follows it is zero.
+__device__ __forceinline__ double basis_scale(double sig) {
+  return __longlong_as_double(__double_as_longlong(sig) & 0x7ff0000000000000ll);
+}
+
 // ------------------------------------------------------- wave reductions --
 // Deterministic sum over the 64 lanes of a wave (fixed butterfly order).
 QMG_HD double wave_sum(double v) {

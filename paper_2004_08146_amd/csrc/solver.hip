@@ -165,13 +165,17 @@ struct Space {
   // One pass leaves an orthogonality error of about eps ||w|| / ||w_new||
   // (<= 20 eps here); the true residual is recomputed after every restart
   // cycle anyway.  The new norm comes out of the update pass.
-  // The basis is stored unnormalised, v_i = sig_i W_i, sig ([nrhs][j + 1]) here and in
+  // The basis is stored unnormalised, v_i = sig_i W_i, sig ([nrhs][j + 2]) here and in
   // dsig ([nrhs][ldsig]) on the device: the projections use sig_i (W_i^H w) and the update
-  // subtracts sig_i^2 (W_i^H w) W_i.  The update's coefficients are formed on the device and
-  // projections and norm are read together, so a pass waits once.
+  // subtracts sig_i^2 (W_i^H w) W_i, after w took a power of two near sig_j, without which
+  // ||W_{j+1}|| would be the product of all h_{i+1,i} and leave the storage type's range.
+  // The update's coefficients are formed on the device and projections and norm are read
+  // together, so a pass waits once.  Fills sig_{j+1} in both places.
+  // A column with sig_j = 0 (dropped, or zero) gets a zero W_{j+1}; act (optional): columns
+  // that are not to decide on a second pass or to be checked.
   // copy (optional): the update pass also writes the new w there in copy_prec.
-  qmg_status arnoldi(std::vector<std::vector<cd>>& h, void* V, int j, void* w,
-                     const std::vector<std::vector<double>>& sig, double* dsig, int ldsig, void* copy = nullptr,
+  qmg_status arnoldi(std::vector<std::vector<cd>>& h, void* V, int j, void* w, std::vector<std::vector<double>>& sig,
+                     double* dsig, int ldsig, const std::vector<char>* act, void* copy = nullptr,
                      int copy_prec = QMG_F64) {
     const int J = j + 1;
     h.assign(nrhs, std::vector<cd>(j + 2, cd(0)));
@@ -182,23 +186,27 @@ struct Space {
     if (!d || !part || !dc) return set_err(c, QMG_E_NOMEM, "out of device memory (Arnoldi)");
     double* hd = host_buf(c, "dots", nres);
     if (!hd) return set_err(c, QMG_E_NOMEM, "out of host memory (Arnoldi)");
-    std::vector<double> before(nrhs), after(nrhs);
+    std::vector<double> before(nrhs), after(nrhs), unscale(nrhs);  // unscale: 1 / scale (0 for 0)
     for (int pass = 0; pass < 2; ++pass) {
-      const int self = pass == 0 ? 1 : 0;
-      hipError_t e = launch_project(p, d, dc, dsig, ldsig, V, vstride(), J, w, n, n, nrhs, part, s, self);
+      const int self = pass == 0 ? 1 : 0, aj = pass == 0 ? j : -1;
+      hipError_t e = launch_project(p, d, dc, dsig, ldsig, V, vstride(), J, w, n, n, nrhs, part, s, self, aj);
       if (e == hipSuccess)
-        e = launch_axpy_sig(p, w, V, vstride(), J, dc, n, n, nrhs, d + nd, dsig, ldsig, J, part, s, copy, copy_prec);
+        e = launch_axpy_sig(p, w, V, vstride(), J, dc, n, n, nrhs, d + nd, dsig, ldsig, aj, J, part, s, copy, copy_prec);
       if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * nres, hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e != hipSuccess) return hip_err(c, e, "Arnoldi step");
       bool again = false;
       for (int k = 0; k < nrhs; ++k) {
+        const double sc = hd[nd + 2 * k + 1];
+        if (pass == 0) unscale[k] = sc > 0.0 ? 1.0 / sc : 0.0;
+        const double fac = pass == 0 ? 1.0 : unscale[k];  // the first pass projects w as it came
         for (int i = 0; i < J; ++i) {
           const double* q = hd + 2 * ((size_t)k * (J + self) + i);
-          h[k][i] += sig[k][i] * cd(q[0], q[1]);
+          h[k][i] += fac * sig[k][i] * cd(q[0], q[1]);
         }
-        if (self) before[k] = hd[2 * ((size_t)k * (J + 1) + J)];
+        if (self) before[k] = sc * sc * hd[2 * ((size_t)k * (J + 1) + J)];
         after[k] = hd[nd + 2 * k];
+        if (act && !(*act)[k]) continue;
         if (!std::isfinite(after[k]) || !std::isfinite(before[k]))
           return set_err(c, QMG_E_NUMERIC, "non-finite norm in Arnoldi step");
         if (after[k] < kReorthRatio2 * before[k]) again = true;
@@ -206,7 +214,11 @@ struct Space {
       }
       if (!again) break;
     }
-    for (int k = 0; k < nrhs; ++k) h[k][j + 1] = std::sqrt(std::max(0.0, after[k]));
+    for (int k = 0; k < nrhs; ++k) {
+      const double wn = std::sqrt(std::max(0.0, after[k]));
+      h[k][j + 1] = unscale[k] * wn;
+      sig[k][j + 1] = wn > 0.0 && std::isfinite(wn) ? 1.0 / wn : 0.0;
+    }
     return QMG_OK;
   }
   // The last Arnoldi step of a restart cycle. Its new vector is never used (the
@@ -269,8 +281,9 @@ qmg_status solver_coarse_gmres(qmg_ctx* c, int p, void* y, const void* r, const 
   st = sp.scale(sp.at(V, 0), r, a);
   if (st != QMG_OK) return st;
   // as in the outer method the basis stays unnormalised after its first vector: the product
-  // A W_j is orthogonalised in place in the next slot, with no scaling pass, and the
-  // solution is a combination of the W_j
+  // A W_j is orthogonalised in place in the next slot, with no scaling pass (its norm stays
+  // near h_{j+1,j}, for any number of steps), and the solution is a combination of the W_j.
+  // A column that is done is dropped (sig = 0): its later vectors are zero.
   hipError_t e = launch_sig_init(dsig, iters + 1, nrhs, s);
   if (e != hipSuccess) return hip_err(c, e, "coarse GMRES");
   std::vector<std::vector<double>> sig(nrhs, std::vector<double>(iters + 1, 0.0));
@@ -281,20 +294,28 @@ qmg_status solver_coarse_gmres(qmg_ctx* c, int p, void* y, const void* r, const 
     e = launch_coarse_apply(c, p, sp.at(V, j + 1), sp.at(V, j), tau, nrhs, s, qform);
     if (e != hipSuccess) return hip_err(c, e, "coarse apply");
     std::vector<std::vector<cd>> h;
-    st = sp.arnoldi(h, V, j, sp.at(V, j + 1), sig, dsig, iters + 1);
+    st = sp.arnoldi(h, V, j, sp.at(V, j + 1), sig, dsig, iters + 1, &act);
     if (st != QMG_OK) return st;
     bool all = true;
+    uint64_t drop = 0;
     for (int k = 0; k < nrhs; ++k) {
-      const double hn = h[k][j + 1].real();
-      sig[k][j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
       if (!act[k]) continue;
+      const double hn = h[k][j + 1].real();
       double est = lsq[k].update(j, h[k]);
       kk[k] = j + 1;
-      if (hn == 0.0 || (tol > 0 && est <= tol * beta[k])) act[k] = 0;
+      if (hn == 0.0 || (tol > 0 && est <= tol * beta[k])) {
+        act[k] = 0;
+        drop |= uint64_t(1) << k;
+        sig[k][j + 1] = 0.0;
+      }
       all = all && !act[k];
     }
     done_it = j + 1;
     if (all || j + 1 == iters) break;
+    if (drop) {
+      e = launch_sig_drop(dsig, iters + 1, j + 1, drop, nrhs, s);
+      if (e != hipSuccess) return hip_err(c, e, "coarse GMRES");
+    }
   }
   int J = 0;
   for (int k = 0; k < nrhs; ++k) J = std::max(J, kk[k]);
@@ -619,7 +640,7 @@ qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, 
       // correction equations) are unchanged by this shortcut
       const bool last = jj + 1 == m && total + 1 < prm->maxiter;
       st = last ? sp.arnoldi_last(h, V, jj, w, sig)
-                : sp.arnoldi(h, V, jj, w, sig, dsig, m + 1, vin ? vc_in : nullptr, zprec);
+                : sp.arnoldi(h, V, jj, w, sig, dsig, m + 1, nullptr, vin ? vc_in : nullptr, zprec);
       if (st != QMG_OK) return st;
       e = mark();
       if (e != hipSuccess) return hip_err(c, e, "event");
@@ -636,10 +657,6 @@ qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, 
       }
       // converged right-hand sides are orthogonalised like the others, so their
       // vectors stay bounded; their coefficients are no longer used
-      for (int i = 0; i < na; ++i) {
-        const double hn = h[i][jj + 1].real();
-        sig[i][jj + 1] = (hn > 0.0 && std::isfinite(hn)) ? 1.0 / hn : 0.0;
-      }
       ++total;
       if (all || jj + 1 == m || total >= prm->maxiter) break;
     }

@@ -41,3 +41,55 @@ def test_device_gmres_many_steps(iters):
     _, _, best = krylov.gmres(lambda v: h.coarse.apply(v, 3.0), rc, iters)
     got = np.linalg.norm(rc - h.coarse.apply(y, 3.0))
     assert abs(got - best) < 1e-9 * np.linalg.norm(rc)
+
+
+def _solve(lat, order, r, taus, iters, tol, prec):
+    real = np.float64 if prec == "f64" else np.float32
+    rd = dev(lex_to_coarse(r, order).view(np.float64).astype(real))
+    out = lat.coarse_solve(lat.coarse(len(taus), prec), rd, taus, len(taus), iters, tol, prec)
+    return coarse_to_lex(host(out).view(real).astype(np.float64).view(np.complex128), order, r.shape[-1] // 2)
+
+
+def _rhs(order, ntv, nrhs, seed=8):
+    rng = np.random.default_rng(seed)
+    return rng.standard_normal((nrhs, len(order), 2 * ntv)) + 1j * rng.standard_normal((nrhs, len(order), 2 * ntv))
+
+
+# Backward error of a solve whose Krylov space is exhausted after 15 (first shift) and 60
+# steps: ||r - A y|| <= tol (||A|| ||y|| + ||r||), ||A|| <= 6.1 here, with the relative error of
+# one coarse apply as tol: 9 * 48 products at 2^-53 and 2^-24, and in BF16 blocks held to 2^-9
+_APPLY_TOL = {"f64": 1e-13, "f32": 2.6e-5, "bf16": 2e-2}
+
+
+def _backward(h, r, y, tau):
+    return np.linalg.norm(r - h.coarse.apply(y, tau)) / (6.1 * np.linalg.norm(y) + np.linalg.norm(r))
+
+
+# host-driven, three right-hand sides, one of them zero; as many steps as the default
+# coarse_maxiter and several times that
+@pytest.mark.parametrize("prec,iters", [("f32", 50), ("f32", 150), ("bf16", 60), ("f64", 120), ("f64", 200)])
+def test_coarse_solve_past_convergence(prec, iters):
+    case("coarse solve %s %d steps" % (prec, iters))
+    _, lat, h, order = _mg(24)
+    r = _rhs(order, 24, 3)
+    r[1] = 0.0
+    taus = [0.02, 0.1, 2.5]
+    y = _solve(lat, order, r, taus, iters, 0.0, prec)
+    assert not y[1].any()
+    for k in (0, 2):
+        assert _backward(h, r[k], y[k], taus[k]) < _APPLY_TOL[prec]
+
+
+# one right-hand side reaches the tolerance in a few steps, the other never does: the first
+# gets the solution it gets alone (the same steps; the batch changes the order of no sum
+# beyond those of the coarse apply), the second the residual it gets alone
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-13), ("f32", 2.6e-5)])
+def test_coarse_solve_mixed_batch(prec, tol):
+    case("coarse solve mixed batch %s" % prec)
+    _, lat, h, order = _mg(24)
+    r, taus, iters = _rhs(order, 24, 2), [0.02, 3.0], 120
+    both = _solve(lat, order, r, taus, iters, 1e-5, prec)
+    alone = [_solve(lat, order, r[k:k + 1], taus[k:k + 1], iters, 1e-5, prec)[0] for k in range(2)]
+    assert np.linalg.norm(both[0] - alone[0]) < tol * np.linalg.norm(alone[0])
+    res = [np.linalg.norm(r[1] - h.coarse.apply(y, 3.0)) / np.linalg.norm(r[1]) for y in (both[1], alone[1])]
+    assert res[1] < 0.2 and abs(res[0] - res[1]) < 1e-3 * res[1]
