@@ -9,7 +9,8 @@
 // vector): each product is orthogonalised in place in the next basis slot, so
 // no scaling pass is needed, and the last step, whose new vector is never used,
 // takes ||w_new||^2 = ||w||^2 - sum_i |v_i^H w|^2 from its dot pass instead of
-// an update pass.
+// an update pass.  The update also gives w a power of two near sig_j, so that
+// ||W_{j+1}|| stays near h_{j+1,j} for any number of steps.
 // One thread per right-hand side; the rotations follow the same convention as
 // the host solver: [[c, s], [-conj(s), c]] [a; b] = [r; 0], c real.
 #include <functional>
@@ -67,10 +68,10 @@ __device__ void gm_sums(const double* partial, int J, int nchunk, double (*out)[
   __syncthreads();
 }
 
-// close column j: h_{j+1,j} = sig_j ||w_new|| (w_new = the projected A W_j,
-// stored as W_{j+1}, so sig_{j+1} = 1 / ||w_new||), rotate, update g; one thread,
+// close column j: h_{j+1,j} = sig_j ||w_new|| / scale (w_new = the projected A W_j times
+// scale, stored as W_{j+1}, so sig_{j+1} = 1 / ||w_new||), rotate, update g; one thread,
 // hc: the column's entries 0..j
-__device__ void gm_close(const GmState& st, int k, int j, double norm2w, double (*hc)[2]) {
+__device__ void gm_close(const GmState& st, int k, int j, double norm2w, double scale, double (*hc)[2]) {
   const int m = st.m;
   double* H = st.H + (int64_t)k * (m + 1) * m * 2;
   double* g = st.g + (int64_t)k * (m + 1) * 2;
@@ -78,7 +79,7 @@ __device__ void gm_close(const GmState& st, int k, int j, double norm2w, double 
   double* sn = st.sn + (int64_t)k * m * 2;
   double* sg = st.sig + (int64_t)k * (m + 1);
   const double wn = sqrt(fmax(norm2w, 0.0));
-  const double hn = sg[j] * wn;
+  const double hn = scale > 0 ? sg[j] / scale * wn : 0.0;
   sg[j + 1] = wn > 0 ? 1.0 / wn : 0.0;
   cpx<double> cur = {hc[0][0], hc[0][1]};
   for (int i = 0; i < j; ++i) {
@@ -108,7 +109,8 @@ __device__ void gm_close(const GmState& st, int k, int j, double norm2w, double 
 }
 
 // One classical Gram-Schmidt pass for w = A W_j, d_i = W_i^H w summed here from the chunk
-// sums: H[i][j] = sig_i sig_j d_i, coef_i = -sig_i^2 d_i (w -= (v_i^H w) v_i).
+// sums: H[i][j] = sig_i sig_j d_i, coef_i = -scale sig_i^2 d_i (w -= (v_i^H w) v_i, times
+// the scale of sig_j).
 // last: the sums also hold ||w||^2 (at index J); the squared norm of the projected w,
 // ||w||^2 - sum_i sig_i^2 |d_i|^2, takes the place of the update pass and the column is
 // closed at once.  One work-group per right-hand side, which also closes the column where
@@ -123,9 +125,10 @@ __global__ __launch_bounds__(kGmWG) void k_gm_coef(GmState st, const double* par
   gm_sums(partial + (int64_t)k * ld * nchunk * 2, ld, nchunk, d);
   const double* sg = st.sig + (int64_t)k * (m + 1);
   if (!last) {
+    const double scale = basis_scale(sg[j]);
     for (int i = threadIdx.x; i < J; i += kGmWG) {
       const cpx<double> di = {d[i][0], d[i][1]};
-      stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * di);
+      stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * scale * di);
       stz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j, (sg[i] * sg[j]) * di);
     }
   } else if (threadIdx.x == 0) {  // scales d in place: no other thread reads it here
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kGmWG) void k_gm_coef(GmState st, const double* par
       d[i][0] *= sg[i] * sg[j];
       d[i][1] *= sg[i] * sg[j];
     }
-    gm_close(st, k, j, fmax(d[J][0] - proj, 0.0), d);
+    gm_close(st, k, j, fmax(d[J][0] - proj, 0.0), 1.0, d);
   }
 }
 
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(kGmWG) void k_gm_col(GmState st, const double* part
     hc[i][1] = h.im;
   }
   gm_sums(partial + (int64_t)k * nchunk * 2, 1, nchunk, nrm);
-  if (threadIdx.x == 0) gm_close(st, k, j, nrm[0][0], hc);
+  if (threadIdx.x == 0) gm_close(st, k, j, nrm[0][0], basis_scale(st.sig[(int64_t)k * (m + 1) + j]), hc);
 }
 
 // y = R^{-1} g (R: the rotated Hessenberg, kk columns) -> coef[k][0..kk)
@@ -247,7 +250,7 @@ static qmg_status gmres_device(qmg_ctx* c, const DevOp& op, void* y, const void*
     if (e == hipSuccess) {
       hipLaunchKernelGGL(k_gm_coef, dim3(nrhs), dim3(kGmWG), lds, s, st, part, nchunk, coef, j, last, longcol);
       if (!last) {
-        e = launch_axpy_partials(cp, w, V, vs, j + 1, coef, n, n, nrhs, part, s);
+        e = launch_axpy_partials(cp, w, V, vs, j + 1, coef, n, n, nrhs, part, s, nullptr, QMG_F64, st.sig, m + 1, j);
         if (e == hipSuccess) hipLaunchKernelGGL(k_gm_col, dim3(nrhs), dim3(kGmWG), lds, s, st, part, nchunk, j, longcol);
       }
       if (e == hipSuccess) e = hipGetLastError();

@@ -93,3 +93,20 @@ def test_coarse_solve_mixed_batch(prec, tol):
     assert np.linalg.norm(both[0] - alone[0]) < tol * np.linalg.norm(alone[0])
     res = [np.linalg.norm(r[1] - h.coarse.apply(y, 3.0)) / np.linalg.norm(r[1]) for y in (both[1], alone[1])]
     assert res[1] < 0.2 and abs(res[0] - res[1]) < 1e-3 * res[1]
+
+
+# the same on the device (V-cycle without smoothing, fixed steps): P^H of its result is y
+@pytest.mark.parametrize("prec,iters", [("f32", 50), ("f32", 100), ("bf16", 50), ("f64", 120)])
+def test_device_gmres_past_convergence(prec, iters):
+    case("device gmres %s %d steps" % (prec, iters))
+    qmg, lat, h, _ = _mg(24)
+    r = random_spinors(DIMS, 3, 41)
+    r[1] = 0.0
+    taus = [0.02, 0.1, 2.5]
+    prm = qmg.default_params(coarse_maxiter=iters, coarse_tol=0.0, nu_post=0, mg_prec=prec)
+    z = host(lat.unpack(lat.vcycle(lat.field(3), lat.pack(dev(r)), taus, 3, prm), 3))
+    assert not z[1].any()
+    # P, the restricted right-hand side and the prolongated solution are rounded to the storage type
+    tol = {"f64": 1e-13, "f32": 2.6e-5, "bf16": 3e-2}[prec]
+    for k in (0, 2):
+        assert _backward(h, mg.restrict(h.P, r[k], BLOCK), mg.restrict(h.P, z[k], BLOCK), taus[k]) < tol
