@@ -5,9 +5,8 @@
 // so Gamma5 P = P Gamma5^c (text before eq. (2.9)).  P is stored complex
 // [nb][2][ntv][6][bs]: column j of aggregate (b, h), entry (spin-in-half,
 // colour) d at site l.  Coarse vectors are [nrhs][nb][2*ntv], index h*ntv + j.
-// Columns of each aggregate are orthonormalised in column order, in two rounds,
-// by Gram-Schmidt over panels of columns (modified Gram-Schmidt in exact
-// arithmetic).
+// Columns of each aggregate are orthonormalised in column order by modified
+// Gram-Schmidt in two rounds over panels of columns.
 #include "qmg_ctx.h"
 #include "reduce.h"
 #include <type_traits>
@@ -36,8 +35,10 @@ __device__ __forceinline__ void panel_sum(double (&v)[NV], double* red) {
 // One work-group per aggregate (b, h), one thread per site.  Panels of kPanel columns are
 // held in registers and orthonormalised in two rounds, each against the columns of the
 // earlier panels (read once per round, all columns of the panel against one of them at a
-// time) and then among themselves in column order; equal to modified Gram-Schmidt in exact
-// arithmetic.  Column by column, as before, every earlier column was read four times per
+// time) and then among themselves: a column is normalised and at once taken out of those
+// after it.  Taken out of a column all together (classical) they left P's columns overlapping where
+// six vectors agree to 1e-10 or better (P^H P y off by 4e-7, at 1e-11 by 2.5e-3), since the second
+// round begins when all columns of the panel had the first.  Column by column, as before, every earlier column was read four times per
 // column from L2: 4.07 ms at 512 blocks of 256 sites and 24 columns, now 0.85 ms, of which
 // reading W, writing P in its three storage types and the 72 re-reads of 24 columns take
 // about 0.6 at the copy rate.
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
 #pragma unroll 1
     for (int round = 0; round < 2; ++round) {
-cpx<double> p[6];
+      cpx<double> p[6];
       auto load = [&](int i) {
 #pragma unroll
         for (int d = 0; d < 6; ++d) p[d] = on ? ldc(P, pidx(g, ntv, b, h, i, d, l)) : czero<double>();
@@ -108,25 +109,7 @@ cpx<double> p[6];
         }
       }
       auto column = [&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        if constexpr (k > 0) {
-          double cf[2 * k];
-#pragma unroll
-          for (int i = 0; i < k; ++i) {
-            cpx<double> a = czero<double>();
-#pragma unroll
-            for (int d = 0; d < 6; ++d) cfma_conj(a, v[i][d], v[k][d]);
-            cf[2 * i] = a.re;
-            cf[2 * i + 1] = a.im;
-          }
-          panel_sum<2 * k>(cf, half());
-#pragma unroll
-          for (int i = 0; i < k; ++i) {
-            const cpx<double> c = {-cf[2 * i], -cf[2 * i + 1]};
-#pragma unroll
-            for (int d = 0; d < 6; ++d) cfma(v[k][d], c, v[i][d]);
-          }
-        }
+        constexpr int k = decltype(kc)::value, M = kPanel - 1 - k;
         double n1[1] = {0.0};
 #pragma unroll
         for (int d = 0; d < 6; ++d) n1[0] += norm2(v[k][d]);
@@ -142,6 +125,24 @@ cpx<double> p[6];
         const double inv = bad || k >= np ? 1.0 : 1.0 / r;
 #pragma unroll
         for (int d = 0; d < 6; ++d) v[k][d] = inv * v[k][d];
+        if constexpr (M > 0) {
+          double cf[2 * M];
+#pragma unroll
+          for (int i = 0; i < M; ++i) {
+            cpx<double> a = czero<double>();
+#pragma unroll
+            for (int d = 0; d < 6; ++d) cfma_conj(a, v[k][d], v[k + 1 + i][d]);
+            cf[2 * i] = a.re;
+            cf[2 * i + 1] = a.im;
+          }
+          panel_sum<2 * M>(cf, half());
+#pragma unroll
+          for (int i = 0; i < M; ++i) {
+            const cpx<double> c = {-cf[2 * i], -cf[2 * i + 1]};
+#pragma unroll
+            for (int d = 0; d < 6; ++d) cfma(v[k + 1 + i][d], c, v[k][d]);
+          }
+        }
       };
       column(std::integral_constant<int, 0>{});
       column(std::integral_constant<int, 1>{});

@@ -48,3 +48,27 @@ def test_interpolation_and_coarse_operator(dims, block, ntv, csw):
         r = lat.restrict(lat.coarse(1, prec), lat.pack(dev(b), prec), 1, prec)
         r = host(r).view(np.complex64).reshape(nb, 2 * ntv)
         assert rel_err(r, mg.restrict(P, b[0], block)[order]) < tol
+
+
+# six and more vectors that agree to 1e-9 .. 1e-11, within and across the panels: P's columns
+# stay orthonormal to the tolerance of the FP64 transfers (P^H P y = y), and the difference of
+# two vectors lies in its range up to the rounding of 2 ntv subtractions of vectors 1 / eps
+# times as large (twice that: maxima against norms)
+@pytest.mark.parametrize("ntv,eps", [(4, 1e-9), (6, 1e-10), (6, 1e-11), (13, 1e-10), (24, 1e-11)])
+def test_interpolation_of_close_vectors(ntv, eps):
+    case("galerkin close vectors ntv %d eps %g" % (ntv, eps))
+    qmg = need_gpu()
+    dims, block = (8, 8, 8, 8), (4, 4, 4, 4)
+    lat = qmg.Lattice(dims, block)
+    lat.set_gauge(dev(random_links(dims, 0.5, seed_for(2, "U"))), -0.8, 0.0)
+    d = random_spinors(dims, ntv + 1, 17)
+    W = d[0][None] + eps * d[1:]
+    lat.set_test_vectors(lat.pack(dev(W)), ntv)
+    rng = np.random.default_rng(6)
+    y = rng.standard_normal((16, 2 * ntv)) + 1j * rng.standard_normal((16, 2 * ntv))
+    v = lat.prolong(lat.field(1), dev(y), 1)
+    got = host(lat.restrict(lat.coarse(1), v, 1)).view(np.complex128).reshape(y.shape)
+    assert rel_err(got, y) < 1e-13
+    w = lat.pack(dev(W[-1] - W[0]))
+    pw = host(lat.unpack(lat.prolong(lat.field(1), lat.restrict(lat.coarse(1), w, 1), 1)))[0]
+    assert rel_err(pw, W[-1] - W[0]) < 4 * ntv * 1.1e-16 / eps
