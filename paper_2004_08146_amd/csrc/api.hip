@@ -63,12 +63,16 @@ void* ws_get(qmg_ctx* c, const std::string& name, size_t bytes) {
 }
 
 void* ws_try(qmg_ctx* c, const std::string& name, size_t bytes, hipStream_t s) {
-  if (s != c->cap_stream || !s) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
+  if (s && s == c->cap_stream) {
+    // the library records a V-cycle: nothing is allocated now; what the eager run before it
+    // could not have, it does without as well
+    auto it = c->ws.find(name);
+    return it != c->ws.end() && it->second.second >= bytes ? it->second.first : nullptr;
+  }
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
   }
   void* p = ws_get(c, name, bytes);
   if (!p) (void)hipGetLastError();
