@@ -57,7 +57,14 @@ void* ws_get(qmg_ctx* c, const std::string& name, size_t bytes) {
     drop_graphs(c);  // captured graphs may hold the old address
   }
   void* p = nullptr;
-  if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) return nullptr;
+  hipError_t e = hipMalloc(&p, std::max<size_t>(bytes, 256));
+  if (e != hipSuccess && name != kHaloName && c->ws.count(kHaloName)) {
+    // memory is short: what this buffer needs comes before scratch that a call can do without
+    (void)hipGetLastError();
+    ws_release(c, kHaloName);
+    e = hipMalloc(&p, std::max<size_t>(bytes, 256));
+  }
+  if (e != hipSuccess) return nullptr;
   c->ws[name] = {p, bytes};
   return p;
 }

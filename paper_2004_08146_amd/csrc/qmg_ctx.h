@@ -104,7 +104,8 @@ void* ws_get(qmg_ctx* c, const std::string& name, size_t bytes);
 // Scratch that a call can do without (nullptr: go the way that needs none): as ws_get,
 // but a failed allocation leaves no HIP error behind, a caller's own stream capture
 // gets none, since a later call may move the buffer under the captured graph, and the
-// library's own capture only what is there.
+// library's own capture only what is there.  ws_get gives kHaloName back when memory is short.
+constexpr char kHaloName[] = "sap_halo";
 void* ws_try(qmg_ctx* c, const std::string& name, size_t bytes, hipStream_t s);
 // Calls on different streams share the scratch: a call's kernels wait for those of the
 // call before it (an event; a recorded V-cycle is bracketed where it is launched).

@@ -413,7 +413,7 @@ hipError_t sweeps(qmg_ctx* c, int p, void* x, const void* f, const double* tau, 
   using P = typename PT<S>::stor;
   const size_t n = field_elems(c);
   const int group = (int)std::max<size_t>(1, std::min<size_t>((size_t)nrhs, kHaloMax / (n * sizeof(cpx<R>))));
-  void* halo = ws_try(c, "sap_halo", n * group * sizeof(cpx<R>), s);
+  void* halo = ws_try(c, kHaloName, n * group * sizeof(cpx<R>), s);
   *done = halo != nullptr;
   if (!*done) return hipSuccess;
   const bool own_capture = c->cap_stream && s == c->cap_stream;

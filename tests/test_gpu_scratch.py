@@ -75,3 +75,27 @@ def test_graph_vcycle_without_room_for_the_halo(tmp_path):
     for k in (0, 5, NRHS - 1):
         one = slice(k * lat.field_bytes(), (k + 1) * lat.field_bytes())
         assert rel_err(host(lat.unpack(short[one])), host(lat.unpack(z[one]))) < 1e-6
+
+
+def test_halo_given_back(tmp_path):
+    """A later call that needs its memory gets it; the smoother goes on without, and with it
+    again once there is room."""
+    case("halo given back")
+    _, lat = _lat(tmp_path, 2)
+    f, x = lat.pack(dev(random_spinors(DIMS, 4, 41)), "f32").repeat(NRHS // 4), lat.field(NRHS, "f32")
+    taus = [0.01 * (k % 7) for k in range(NRHS)]
+    ref = lat.sap_smooth(x.clone(), f, taus, NRHS, 2, 2, "f32").clone()  # allocates the halo
+    y, yo = lat.coarse(NRHS, "f32"), lat.coarse(NRHS, "f32")
+    y.view(torch.float32).normal_()
+    x2 = x.clone()
+    full = _fill()
+    try:
+        # a basis of 121 vectors of 64 x 512 x 16 complex entries: 508 MB
+        lat.coarse_solve(yo, y, taus, NRHS, 120, 1e-4, "f32")
+        lat.sap_smooth(x2, f, taus, NRHS, 2, 2, "f32")
+        torch.cuda.synchronize()
+    finally:
+        del full
+        torch.cuda.empty_cache()
+    assert rel_err(x2.view(torch.float32).cpu(), ref.view(torch.float32).cpu()) < 1e-6
+    assert torch.equal(lat.sap_smooth(x, f, taus, NRHS, 2, 2, "f32"), ref)
