@@ -193,6 +193,77 @@ __device__ __forceinline__ Link<C> ld_link44(const P* U, uint32_t b, int mu, uin
   return u;
 }
 
+// The arithmetic that the two 4^4 kernels share, with every rounding written out: left to
+// itself the compiler fuses one or the other product of a sum, another one in each kernel, and
+// a column's last digits would depend on the batch by which the launch picks between them.
+template <typename C>
+__device__ __forceinline__ cpx<C> mul44(cpx<C> a, cpx<C> b) {
+  return {fmar(a.re, b.re, -(a.im * b.im)), fmar(a.re, b.im, a.im * b.re)};
+}
+template <typename C>
+__device__ __forceinline__ cpx<C> mul_conj44(cpx<C> a, cpx<C> b) {
+  return {fmar(a.re, b.re, a.im * b.im), fmar(a.re, b.im, -(a.im * b.re))};
+}
+template <typename C>
+__device__ __forceinline__ Half<C> umul44(const Link<C>& U, const Half<C>& h) {
+  Half<C> o;
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cpx<C> t = mul44(U.u[a][0], h.h[s][0]);
+      cfma(t, U.u[a][1], h.h[s][1]);
+      cfma(t, U.u[a][2], h.h[s][2]);
+      o.h[s][a] = t;
+    }
+  return o;
+}
+template <typename C>
+__device__ __forceinline__ Half<C> udagmul44(const Link<C>& U, const Half<C>& h) {
+  Half<C> o;
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cpx<C> t = mul_conj44(U.u[0][a], h.h[s][0]);
+      cfma_conj(t, U.u[1][a], h.h[s][1]);
+      cfma_conj(t, U.u[2][a], h.h[s][2]);
+      o.h[s][a] = t;
+    }
+  return o;
+}
+// w = one Hermitian 6x6 block (ld(k): its k-th stored entry) times v
+template <typename C, typename F>
+__device__ __forceinline__ void block44(cpx<C> (&w)[6], const cpx<C> (&v)[6], F&& ld) {
+  C d[6];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const cpx<C> t = ld(k);
+    d[2 * k] = t.re;
+    d[2 * k + 1] = t.im;
+  }
+  int k = 3;
+#pragma unroll
+  for (int i = 1; i < 6; ++i)
+#pragma unroll
+    for (int j = 0; j < i; ++j) {
+      const cpx<C> a = ld(k), p = mul44(a, v[j]), q = mul_conj44(a, v[i]);
+      ++k;
+      // the diagonal enters with a row's first product
+      w[i] = j == 0 ? cpx<C>{fmar(d[i], v[i].re, p.re), fmar(d[i], v[i].im, p.im)} : w[i] + p;
+      w[j] = i == 1 ? cpx<C>{fmar(d[j], v[j].re, q.re), fmar(d[j], v[j].im, q.im)} : w[j] + q;
+    }
+}
+// (D - tau Gamma5) psi (MODE 0) or (Gamma5 D - tau) psi at one entry of chirality H: o the
+// diagonal part, hops the sum of the hops
+template <typename C, int MODE, int H>
+__device__ __forceinline__ cpx<C> tail44(cpx<C> o, cpx<C> hops, cpx<C> psi, C tau) {
+  const cpx<C> v = {fmar(C(-0.5), hops.re, o.re), fmar(C(-0.5), hops.im, o.im)};
+  if (H == 0) return {fmar(-tau, psi.re, v.re), fmar(-tau, psi.im, v.im)};
+  if (MODE == 0) return {fmar(tau, psi.re, v.re), fmar(tau, psi.im, v.im)};
+  return {fmar(-tau, psi.re, -v.re), fmar(-tau, psi.im, -v.im)};
+}
+
 // (m0 + 4 + C) psi with the two Hermitian 6x6 blocks of (b, l)
 template <typename C, typename P>
 __device__ __forceinline__ Spinor<C> diag44(const P* D, uint32_t b, uint32_t l, const Spinor<C>& p) {
@@ -202,26 +273,10 @@ __device__ __forceinline__ Spinor<C> diag44(const P* D, uint32_t b, uint32_t l, 
     cpx<C> v[6], w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) v[i] = p.s[2 * h + i / 3][i % 3];
-    auto ld = [&](int k) {
+    block44(w, v, [&](int k) {
       const auto d = cv(ldo(D, ((b * 36u + (uint32_t)(18 * h + k)) << 8) + l));
       return cpx<C>{C(d.re), C(d.im)};
-    };
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const cpx<C> d = ld(k);
-      w[2 * k] = d.re * v[2 * k];
-      w[2 * k + 1] = d.im * v[2 * k + 1];
-    }
-    int k = 3;
-#pragma unroll
-    for (int i = 1; i < 6; ++i)
-#pragma unroll
-      for (int j = 0; j < i; ++j) {
-        const cpx<C> a = ld(k);
-        ++k;
-        w[i] = w[i] + a * v[j];
-        w[j] = w[j] + cmul_conj(a, v[i]);
-      }
+    });
 #pragma unroll
     for (int i = 0; i < 6; ++i) o.s[2 * h + i / 3][i % 3] = w[i];
   }
@@ -260,7 +315,7 @@ __device__ __forceinline__ void l44_face(Half<C>& fh, Half<C>& fw, const PI* in,
   const Spinor<C> pf = ld_spinor44<C>(in, (uint32_t)nbr[b * 8 + 2 * MU], l44_site<MU>(j, 0));
   const Spinor<C> pb = ld_spinor44<C>(in, (uint32_t)nbr[b * 8 + 2 * MU + 1], l44_site<MU>(j, 3));
   fh = project(pf, MU, true);
-  fw = udagmul(u, project(pb, MU, false));
+  fw = udagmul44(u, project(pb, MU, false));
 }
 
 template <typename C, int MU, bool TWO>
@@ -276,7 +331,7 @@ __device__ __forceinline__ void l44_dir(Spinor<C>& acc, const Spinor<C>& psi, co
     for (int i = 0; i < 6; ++i) hb[i * 256 + l] = h.h[i / 3][i % 3];
   }
   {
-    const Half<C> w = udagmul(u, project(psi, MU, false));
+    const Half<C> w = udagmul44(u, project(psi, MU, false));
     if (lc != 3u)
 #pragma unroll
       for (int i = 0; i < 6; ++i) wb[i * 256 + l] = w.h[i / 3][i % 3];
@@ -293,7 +348,7 @@ __device__ __forceinline__ void l44_dir(Spinor<C>& acc, const Spinor<C>& psi, co
   Half<C> h, w;
 #pragma unroll
   for (int i = 0; i < 6; ++i) h.h[i / 3][i % 3] = hb[i * 256 + lf];
-  accum_recon(acc, umul(u, h), MU, true);
+  accum_recon(acc, umul44(u, h), MU, true);
 #pragma unroll
   for (int i = 0; i < 6; ++i) w.h[i / 3][i % 3] = wb[i * 256 + lb];
   accum_recon(acc, w, MU, false);
@@ -372,12 +427,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        cpx<C> v = o.s[s][c] - C(0.5) * acc.s[s][c];
-        if (MODE == 0) v = (s < 2) ? v - tau * psi.s[s][c] : v + tau * psi.s[s][c];
-        else v = (s < 2) ? v - tau * psi.s[s][c] : -v - tau * psi.s[s][c];
-        o.s[s][c] = v;
-      }
+      for (int c = 0; c < 3; ++c)
+        o.s[s][c] = s < 2 ? tail44<C, MODE, 0>(o.s[s][c], acc.s[s][c], psi.s[s][c], tau)
+                          : tail44<C, MODE, 1>(o.s[s][c], acc.s[s][c], psi.s[s][c], tau);
     if (a.nt_out) {
 #pragma unroll
       for (int i = 0; i < 12; ++i) sto_nt(out, ((b * 12u + (uint32_t)i) << 8) + l, vc(o.s[i / 3][i % 3], (P*)nullptr));
@@ -391,25 +443,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // ---- 4^4 blocks, few of them: a work-group is a quarter of a block (64 sites), wave w
 // takes the two hops of direction w, so that a site's 8 hops are one round of loads instead
-// of a chain of them, and there are four times as many work-groups.
+// of a chain of them, and there are four times as many work-groups.  The half spinors of all
+// hops meet in LDS and are added in the order of k_dslash44l, so that a column's result does
+// not depend, in rounding, on the batch by which the launch picks between the two.
 template <typename C, int MU, typename PI, typename P>
-__device__ __forceinline__ void s44_pair(Spinor<C>& acc, const PI* in, const P* U, const int* nbr, uint32_t b,
-                                         uint32_t l) {
+__device__ __forceinline__ void s44_pair(cpx<C> (*part)[6][64], const PI* in, const P* U, const int* nbr, uint32_t b,
+                                         uint32_t l, uint32_t lane) {
   constexpr int SH = kL44Sh[MU];
   const uint32_t lc = (l >> SH) & 3u;
   const uint32_t bf = lc == 3u ? (uint32_t)nbr[b * 8 + 2 * MU] : b, bb = lc == 0u ? (uint32_t)nbr[b * 8 + 2 * MU + 1] : b;
   const uint32_t lf = lc == 3u ? l - (3u << SH) : l + (1u << SH), lb = lc == 0u ? l + (3u << SH) : l - (1u << SH);
   const Spinor<C> pf = ld_spinor44<C>(in, bf, lf), pb = ld_spinor44<C>(in, bb, lb);
   const Link<C> uf = ld_link44<C>(U, b, MU, l), ub = ld_link44<C>(U, bb, MU, lb);
-  accum_recon(acc, umul(uf, project(pf, MU, true)), MU, true);
-  accum_recon(acc, udagmul(ub, project(pb, MU, false)), MU, false);
+  const Half<C> hf = umul44(uf, project(pf, MU, true)), hb = udagmul44(ub, project(pb, MU, false));
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    part[2 * MU][c][lane] = hf.h[c / 3][c % 3];
+    part[2 * MU + 1][c][lane] = hb.h[c / 3][c % 3];
+  }
+}
+// the sum of the eight hops, as l44_dir forms it
+template <typename C, int MU>
+__device__ __forceinline__ void s44_add(Spinor<C>& acc, const cpx<C> (*part)[6][64], uint32_t lane) {
+  Half<C> hf, hb;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    hf.h[c / 3][c % 3] = part[2 * MU][c][lane];
+    hb.h[c / 3][c % 3] = part[2 * MU + 1][c][lane];
+  }
+  accum_recon(acc, hf, MU, true);
+  accum_recon(acc, hb, MU, false);
 }
 
 template <typename S, bool CLOVER, int MODE, typename SI>
 __global__ __launch_bounds__(256) void k_dslash44s(DsArgs<S, SI> a) {
   using C = typename PT<S>::real;
   using P = typename PT<S>::stor;
-  __shared__ cpx<C> part[4][12][64];
+  __shared__ cpx<C> part[8][6][64];
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   const uint32_t l = ((blockIdx.x & 3u) << 6) | lane, i = blockIdx.x >> 2;
   const uint32_t b = i / (uint32_t)a.nrhs, k = i - b * (uint32_t)a.nrhs;
@@ -429,51 +499,39 @@ __global__ __launch_bounds__(256) void k_dslash44s(DsArgs<S, SI> a) {
         dg[c] = cpx<C>{C(t.re), C(t.im)};
       }
   }
-  Spinor<C> acc;
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
-  if (wave == 0) s44_pair<C, 0>(acc, in, a.U, a.g.nbr, b, l);
-  else if (wave == 1) s44_pair<C, 1>(acc, in, a.U, a.g.nbr, b, l);
-  else if (wave == 2) s44_pair<C, 2>(acc, in, a.U, a.g.nbr, b, l);
-  else s44_pair<C, 3>(acc, in, a.U, a.g.nbr, b, l);
-#pragma unroll
-  for (int c = 0; c < 12; ++c) part[wave][c][lane] = acc.s[c / 3][c % 3];
+  if (wave == 0) s44_pair<C, 0>(part, in, a.U, a.g.nbr, b, l, lane);
+  else if (wave == 1) s44_pair<C, 1>(part, in, a.U, a.g.nbr, b, l, lane);
+  else if (wave == 2) s44_pair<C, 2>(part, in, a.U, a.g.nbr, b, l, lane);
+  else s44_pair<C, 3>(part, in, a.U, a.g.nbr, b, l, lane);
   __syncthreads();
-  if (wave >= 2) return;
-  cpx<C> w[6];
-  if (CLOVER) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      w[2 * q] = dg[q].re * v[2 * q];
-      w[2 * q + 1] = dg[q].im * v[2 * q + 1];
-    }
-    int q = 3;
-#pragma unroll
-    for (int r = 1; r < 6; ++r)
-#pragma unroll
-      for (int j = 0; j < r; ++j) {
-        w[r] = w[r] + dg[q] * v[j];
-        w[j] = w[j] + cmul_conj(dg[q], v[r]);
-        ++q;
-      }
-  } else {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) w[c] = C(a.mass4) * v[c];
-  }
   const C tau = C(a.tau[k]);
-  P* out = a.out + (size_t)k * a.fstride;
+  typename PT<S>::stor* out = a.out + (size_t)k * a.fstride;
+  auto finish = [&](auto hc) {
+    constexpr int H = decltype(hc)::value;
+    Spinor<C> acc;
 #pragma unroll
-  for (int c = 0; c < 6; ++c) {
-    const uint32_t at = 6u * wave + (uint32_t)c;
-    const cpx<C> hops = ((part[0][at][lane] + part[1][at][lane]) + part[2][at][lane]) + part[3][at][lane];
-    cpx<C> r = w[c] - C(0.5) * hops;
-    if (wave == 0) r = r - tau * v[c];
-    else if (MODE == 0) r = r + tau * v[c];
-    else r = -r - tau * v[c];
-    sto(out, ((b * 12u + at) << 8) + l, vc(r, (P*)nullptr));
-  }
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
+    s44_add<C, 0>(acc, part, lane);
+    s44_add<C, 1>(acc, part, lane);
+    s44_add<C, 2>(acc, part, lane);
+    s44_add<C, 3>(acc, part, lane);
+    cpx<C> w[6];
+    if constexpr (CLOVER) {
+      block44(w, v, [&](int q) { return dg[q]; });
+    } else {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) w[c] = C(a.mass4) * v[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const cpx<C> r = tail44<C, MODE, H>(w[c], acc.s[2 * H + c / 3][c % 3], v[c], tau);
+      sto(out, ((b * 12u + 6u * H + (uint32_t)c) << 8) + l, vc(r, (P*)nullptr));
+    }
+  };
+  if (wave == 0) finish(std::integral_constant<int, 0>{});
+  else if (wave == 1) finish(std::integral_constant<int, 1>{});
 }
 
 template <typename S, bool CLOVER, int MODE, bool HOLD, typename SI>

@@ -52,3 +52,29 @@ def test_stencil_selection_sampled(dims, nrhs, prec, tol):
     for k in sorted({0, nrhs - 1}):
         ref = oracle_at_sites(U, host(pin[k]), -0.8, 1.0, sites, taus[k])
         assert rel_err([host(q[k][x]) for x in sites], ref) < tol
+
+
+# a column alone and in batches that take other kernels: few-block kernel and the one that
+# holds a block (8^4 and 16x8^3, FP64 from 9 and 5, FP32 and BF16 from 17 and 9 right-hand
+# sides), links held or not (FP32), free and fixed order of loads on other blocks; bit for bit
+@pytest.mark.parametrize("dims,block,batches", [((8, 8, 8, 8), (4, 4, 4, 4), (3, 9, 17)),
+                                                ((16, 8, 8, 8), (4, 4, 4, 4), (5, 9, 12)),
+                                                ((16, 16, 16, 8), (4, 4, 4, 4), (2, 5)),
+                                                ((8, 8, 8, 8), (4, 4, 4, 2), (2, 17, 20)),
+                                                ((16, 8, 8, 8), (8, 4, 4, 2), (2, 3))])
+@pytest.mark.parametrize("prec", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("csw", [0.0, 1.0])
+def test_stencil_independent_of_batch(dims, block, batches, prec, csw):
+    case("stencil batches %s %s %s csw %g" % (dims, block, prec, csw))
+    qmg = need_gpu()
+    lat = qmg.Lattice(dims, block)
+    lat.set_gauge(dev(random_links(dims, 0.5, seed_for(2, "U"))), -0.8, csw)
+    n = max(batches)
+    fin, fb = lat.pack(dev(random_spinors(dims, n, seed_for(2, "b"))), prec), lat.field_bytes(prec)
+    taus = [0.03 * (k + 1) for k in range(n)]
+    for apply in (lat.apply_Q_shifted, lat.apply_A):
+        ref = [apply(lat.field(1, prec), fin[k * fb:(k + 1) * fb], taus[k:k + 1], 1, prec) for k in range(n)]
+        for m in batches:
+            out = apply(lat.field(m, prec), fin[:m * fb], taus[:m], m, prec)
+            for k in range(m):
+                assert torch.equal(out[k * fb:(k + 1) * fb], ref[k]), (m, k)
