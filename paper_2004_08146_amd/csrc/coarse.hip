@@ -90,6 +90,55 @@ __global__ __launch_bounds__(576) void k_coarse_apply(const int* nbr, int nb, ty
   }
 }
 
+// The same on many coarse sites: one wave per site takes the nine entries in turn.  There a
+// launch is bound by what all its waves issue and load, of which nine of them spend more (the
+// sum through LDS, nine times the idle lanes): 4096 sites, FP64, ntv 20, 1 rhs 276 us against 138.
+template <typename S, typename C, int T>
+__global__ __launch_bounds__(64) void k_coarse_apply1(const int* nbr, int nb, typename PT<C>::stor* out,
+                                                      const typename PT<S>::stor* DcT, const typename PT<C>::stor* in,
+                                                      int nc, int nrhs, TauArr tau) {
+  using R = typename PT<C>::real;
+  __shared__ cpx<R> xin[9][T][64];
+  const int b = blockIdx.x, k0 = blockIdx.y * T, i = threadIdx.x;
+  // all lanes load, also where rows are short (ntv 5, 4 rhs a lane's row each: 1.2 times slower)
+  for (int e = i; e < 9 * T * nc; e += 64) {
+    const int d = e / (T * nc), t = e / nc % T, j = e % nc;
+    const int nbk = d == 0 ? b : nbr[b * 8 + d - 1];
+    xin[d][t][j] = k0 + t < nrhs ? ldcv<R>(in, ((int64_t)(k0 + t) * nb + nbk) * nc + j) : czero<R>();
+  }
+  __syncthreads();
+  if (i >= nc) return;
+  cpx<R> acc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) acc[t] = czero<R>();
+  const R g5 = i < nc / 2 ? R(1) : R(-1);
+  for (int d = 0; d < 9; ++d) {
+    if (d == 0 || (d & 1)) {
+      const auto* Dd = DcT + ((int64_t)b * 5 + (d + 1) / 2) * nc * nc + i;
+      for (int j = 0; j < nc; ++j) {
+        const cpx<R> a = ldcv<R>(Dd, (int64_t)j * nc);
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = acc[t] + a * xin[d][t][j];
+      }
+    } else {
+      const auto* Fd = DcT + ((int64_t)nbr[b * 8 + d - 1] * 5 + d / 2) * nc * nc + (int64_t)i * nc;
+      for (int j = 0; j < nc; ++j) {
+        const cpx<R> f = ldcv<R>(Fd, j);
+        const R gg = j < nc / 2 ? g5 : -g5;
+        const cpx<R> a = {gg * f.re, -gg * f.im};
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = acc[t] + a * xin[d][t][j];
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    if (k0 + t < nrhs) {
+      const cpx<R> v = acc[t] - (R(tau.t[k0 + t]) * g5) * xin[0][t][i];
+      stcv(out, ((int64_t)(k0 + t) * nb + b) * nc + i, tau.qform ? g5 * v : v);
+    }
+}
+
 // ---- MFMA coarse apply: per coarse site b and tile of 16 columns, Out (2ntv x 16) =
 // sum_d D_c[b][d] (2ntv x 2ntv) In_{nbr(b,d)} (2ntv x 16).
 typedef float mf4 __attribute__((ext_vector_type(4)));
@@ -273,11 +322,17 @@ void capply_mfma(const CLevel& lv, void* out, const void* in, const TauArr& tau,
 }
 
 template <typename S, int T>
-void capply_t(const CLevel& lv, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
+void capply_t(const CLevel& lv, bool one, void* out, const void* in, const TauArr& tau, int nrhs, hipStream_t s) {
   using P = typename PT<CT<S>>::stor;
   const int nc = 2 * lv.ntv;
-  hipLaunchKernelGGL((k_coarse_apply<S, CT<S>, T>), dim3(lv.nb, (nrhs + T - 1) / T), dim3(576), 0, s, lv.nbr, lv.nb,
-                     (P*)out, (const typename PT<S>::stor*)lv.D, (const P*)in, nc, nrhs, tau);
+  const dim3 grid(lv.nb, (nrhs + T - 1) / T);
+  const auto* D = (const typename PT<S>::stor*)lv.D;
+  if (one)
+    hipLaunchKernelGGL((k_coarse_apply1<S, CT<S>, T>), grid, dim3(64), 0, s, lv.nbr, lv.nb, (P*)out, D, (const P*)in, nc,
+                       nrhs, tau);
+  else
+    hipLaunchKernelGGL((k_coarse_apply<S, CT<S>, T>), grid, dim3(576), 0, s, lv.nbr, lv.nb, (P*)out, D, (const P*)in, nc,
+                       nrhs, tau);
 }
 
 template <typename S>
@@ -300,9 +355,28 @@ void capply_s(const qmg_ctx* c, const CLevel& lv, void* out, const void* in, con
     if (lv.ntv == 16) return capply_mfma<S, 2>(lv, out, in, t, nrhs, s);
     if (lv.ntv == 8) return capply_mfma<S, 1>(lv, out, in, t, nrhs, s);
   }
-  if (nrhs >= 3) capply_t<S, 4>(lv, out, in, t, nrhs, s);
-  else if (nrhs == 2) capply_t<S, 2>(lv, out, in, t, nrhs, s);
-  else capply_t<S, 1>(lv, out, in, t, nrhs, s);
+  // One wave per site or nine.  From 4 rhs on by the rounds that the work-groups of 4 rhs take:
+  // 256 (FP64) or 512 of nine waves run at a time, four times as many of one wave, and a round
+  // of those takes 3.4 times as long (nine / one, FP64 512 sites: 4 rhs 0.6, 8 rhs 1.15, 12 rhs
+  // 0.9; FP32 1024 sites: 4 rhs 0.8, 8 rhs 1.3, 12 rhs 1.0; 2048 and more: 1.0-1.3 everywhere).
+  // Fewer rhs: FP64 512 sites 0.6-1.1, 1024 1.2-1.5, more 1.3-2.3; FP32 and bf16, 1 or 2 rhs,
+  // are better with nine (0.2-1.0) but for short rows on 4096 sites and more (ntv 5 and 12:
+  // 1.0-1.6; bf16, 1 rhs, from 8192), 3 rhs from 1024 sites on 1.0-2.2.  3 rhs are three times one rhs where the rows
+  // are short or the blocks stay in the caches (2048 sites, ntv 28, FP32 0.75 against 1.1).
+  constexpr bool f64 = std::is_same<S, double>::value;
+  bool one;
+  if (nrhs >= 4) {
+    constexpr int64_t kRun = f64 ? 256 : 512;
+    const int64_t wgs = (int64_t)lv.nb * ((nrhs + 3) / 4);
+    one = 10 * ((wgs + kRun - 1) / kRun) >= 34 * ((wgs + 4 * kRun - 1) / (4 * kRun));
+  } else {
+    const int few = std::is_same<S, bf16_t>::value && nrhs == 1 ? 8192 : 4096;
+    one = nrhs == 3 || f64 ? lv.nb >= 1024 : lv.nb >= few && lv.ntv <= 12;
+  }
+  const bool three = nrhs == 3 && one && (lv.ntv <= 20 || bytes <= 128 * (int64_t(1) << 20));
+  if (nrhs >= 3 && !three) capply_t<S, 4>(lv, one, out, in, t, nrhs, s);
+  else if (nrhs == 2) capply_t<S, 2>(lv, one, out, in, t, nrhs, s);
+  else capply_t<S, 1>(lv, one, out, in, t, nrhs, s);
 }
 
 }  // namespace

@@ -97,3 +97,32 @@ def test_coarse_apply_matrix_cores(dims, block, ntv, nrhs, prec, tol):
     out = coarse_to_lex(host(og).view(real).astype(np.float64).view(np.complex128), order, ntv)
     for k in range(nrhs):
         assert rel_err(out[k], h.coarse.apply(y[k], taus[k])) < tol
+
+
+# one wave per site: 512 and 1024 sites, where it takes over from nine (FP64: 1, 2, 4 and 8 right-hand
+# sides, 3 of them one at a time; FP32: 3 and 8), and rows longer than half a wave; Q form by
+# the V-cycle tests.  rel. 1e-13 and 2.6e-5 as above
+@pytest.mark.parametrize("dims,ntv,nrhs", [((8, 8, 8, 16), 5, 4), ((8, 8, 8, 16), 5, 8), ((8, 8, 16, 16), 12, 1),
+                                           ((8, 8, 16, 16), 12, 2), ((8, 8, 16, 16), 12, 3), ((8, 8, 16, 16), 5, 9),
+                                           ((8, 8, 16, 16), 20, 3), ((8, 8, 16, 16), 28, 3)])
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-13), ("f32", 2.6e-5)])
+def test_coarse_apply_many_sites(dims, ntv, nrhs, prec, tol):
+    case("coarse apply many sites %s ntv %d nrhs %d %s" % (dims, ntv, nrhs, prec))
+    qmg = need_gpu()
+    block = (2, 2, 2, 2)
+    U = random_links(dims, 0.5, seed_for(2, "U"))
+    op = dirac.Operator(U, -0.8, None)
+    lat = qmg.Lattice(dims, block)
+    lat.set_gauge(dev(U), -0.8, 0.0)
+    W = random_test_vectors(dims, ntv, seed_for(2, "W"))
+    lat.set_test_vectors(lat.pack(dev(W)), ntv)
+    P, order = mg.build_P(W, block), lat.coarse_site_order()
+    rng = np.random.default_rng(8)
+    y = rng.standard_normal((nrhs, len(order), 2 * ntv)) + 1j * rng.standard_normal((nrhs, len(order), 2 * ntv))
+    taus = [0.02 * (k + 1) for k in range(nrhs)]
+    real = np.float64 if prec == "f64" else np.float32
+    yd = dev(lex_to_coarse(y, order).view(np.float64).astype(real))
+    og = lat.apply_coarse(lat.coarse(nrhs, prec), yd, taus, nrhs, prec)
+    out = coarse_to_lex(host(og).view(real).astype(np.float64).view(np.complex128), order, ntv)
+    for k in sorted({0, nrhs - 1}):
+        assert rel_err(out[k], mg.restrict(P, op.A(mg.prolong(P, y[k], dims, block), taus[k]), block)) < tol
