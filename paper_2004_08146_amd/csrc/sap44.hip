@@ -280,7 +280,7 @@ void k_sap44h(Sap44Args<S> a) {
   }
   const Link<R> u0f = half_link<R>(a.U, b, 0, l), u0b = half_link<R>(a.U, b, 0, x0 > 0 ? l - 64u : l);
   cpx<R> dg[2][18];
-  if (CLOVER) {
+  if (CLOVER && a.solve) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
