@@ -33,12 +33,20 @@
  * and tau arrays are HOST pointers.  The library copies what it keeps
  * (gauge field, clover term, interpolation, coarse operator) and holds no
  * caller pointer after a call returns.  Workspace is allocated lazily and
- * released by qmg_destroy.
+ * released by qmg_destroy.  SAP on 4^4 blocks (qmg_sap_smooth, V-cycles,
+ * solves, setup) also keeps a halo field as large as the fields it smooths
+ * together, in FP64 or FP32, at most 8 GiB per context; it is given back when
+ * another buffer of the context finds no memory.
  *
  * Asynchrony: compute calls enqueue on `stream` and return without waiting,
  * except qmg_set_gauge, qmg_set_test_vectors, qmg_setup_mg, qmg_field_dot,
  * qmg_coarse_solve, qmg_vcycle, qmg_solve_shifted and qmg_autotune, which
- * synchronise the stream.
+ * synchronise the stream.  A call that has to enlarge workspace waits for
+ * the device once.  Calls of one context on different streams take turns with
+ * the halo field of SAP.  While the caller captures `stream`, and where there
+ * is no memory for that field, SAP gathers its neighbours instead: no scratch,
+ * slower, and another order of sums, so results differ in the last digits
+ * from those of an uncaptured call.
  *
  * Errors: the return code is the only channel (no C++ exception crosses the
  * interface); qmg_last_error gives a message.  A context is not thread safe.
@@ -220,7 +228,9 @@ qmg_status qmg_prolong(qmg_ctx* ctx, void* v, const void* yc, int nrhs, qmg_prec
 qmg_status qmg_apply_coarse(qmg_ctx* ctx, void* out, const void* in, const double* tau,
                             int nrhs, qmg_prec p, hipStream_t stream);
 /* Coarse GMRES from zero on (D_c - tau_k Gamma5^c) y_k = r_k, for exactly
- * `iters` steps when tol <= 0, else until ||res|| <= tol ||r_k||. */
+ * `iters` steps when tol <= 0 (any number: steps beyond convergence change the
+ * solution by rounding only), else until ||res|| <= tol ||r_k||, each column
+ * by itself, at most `iters` steps. */
 qmg_status qmg_coarse_solve(qmg_ctx* ctx, void* y, const void* r, const double* tau, int nrhs,
                             int iters, double tol, qmg_prec p, hipStream_t stream);
 /* One V-cycle z_k = M r_k (no pre-smoothing, coarse solve, nu_post SAP sweeps). */

@@ -353,16 +353,6 @@ hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, 
   return hipGetLastError();
 }
 
-// as launch_axpy_partials; norms[2k] = ||w_k||^2 afterwards (fixed summation order)
-hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
-                            int64_t stride, int nrhs, double* norms, double* partial, hipStream_t s, void* copy,
-                            int copy_prec) {
-  const hipError_t e = launch_axpy_partials(p, w, V, vstride, J, coef, n, stride, nrhs, partial, s, copy, copy_prec);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_dot_stage2, dim3(1, nrhs), dim3(256), 0, s, norms, partial, 1, dot_chunks(n));
-  return hipGetLastError();
-}
-
 hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
                           int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
                           hipStream_t s, int with_self, int aj) {
@@ -394,7 +384,7 @@ hipError_t launch_sig_init(double* sig, int ldsig, int nrhs, hipStream_t s) {
   return hipGetLastError();
 }
 
-// scratch needed by launch_multidot / launch_axpy_norm: doubles
+// scratch needed by launch_multidot, launch_dot_partials and launch_axpy_partials: doubles
 size_t multidot_partial_doubles(int64_t n, int J, int nrhs) {
   return (size_t)((n + kChunk - 1) / kChunk) * (J + 1) * nrhs * 2;
 }

@@ -7,8 +7,7 @@
 // eq. (2.9)), so Gamma5^c D_c Gamma5^c = D_c^H and, hop type by hop type, the
 // block coupling b to X - mu is Gamma5^c (the block coupling X - mu to b)^H
 // Gamma5^c.  The apply kernels rebuild those backward blocks on the fly.
-// Blocks are
-// stored transposed, DcT[b][e][j][i] = D_c[b][e]_{ij}, e = 0 self, 1 + mu for
+// Blocks are stored transposed, DcT[b][e][j][i] = D_c[b][e]_{ij}, e = 0 self, 1 + mu for
 // the block at X + mu (kept apart from the -mu coupling even when the two
 // neighbours coincide).  In the 9-entry stencil numbering used by the kernels,
 // d = 0 is self, d = 1 + 2 mu the block at X + mu, d = 2 + 2 mu the one at
@@ -170,9 +169,10 @@ __device__ __forceinline__ void ld4s(const uint32_t* p, uint32_t* f) {
   f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w;
 }
 
-// One wave per 16-row tile t, the waves share the staged inputs.  PACK: up to 8 right-hand sides, columns 0-7 their real parts and
-// 8-15 their imaginary parts, two real products per step of 4 (the staged pair is (re, -im)
-// or (im, re)); else 16 right-hand sides per tile and four products.
+// One wave per 16-row tile t, the waves share the staged inputs.  PACK: up to 8 right-hand
+// sides, columns 0-7 their real parts and 8-15 their imaginary parts, two real products per
+// step of 4 (the staged pair is (re, -im) or (im, re)); else 16 right-hand sides per tile and
+// four products.
 // Backward blocks: sum_j g_i g_j conj(F_ji) y_j = g_i conj(sum_j F_ji conj(g_j y_j)), so the
 // staged input takes g_j and the conjugation and the sum, kept apart, the rest.
 // Each run of 16 contraction indices goes in the order j = jb + 4 lk + q (step q): a lane's

@@ -304,7 +304,7 @@ __device__ __forceinline__ uint32_t l44_site(uint32_t j, uint32_t v) {
   else return (j << 2) | v;
 }
 
-template <typename C, int MU, typename PI, typename P>
+template <typename C, int MU, typename P>
 __device__ __forceinline__ void l44_face_link(Link<C>& u, const P* U, const int* nbr, uint32_t b, uint32_t j) {
   u = ld_link44<C>(U, (uint32_t)nbr[b * 8 + 2 * MU + 1], MU, l44_site<MU>(j, 3));
 }
@@ -372,10 +372,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int* nbr = a.g.nbr;
   Link<C> u[HOLD ? 4 : 1], uf;
   auto face_link = [&](uint32_t j) {
-    if (wave == 0) l44_face_link<C, 0, PI>(uf, a.U, nbr, b, j);
-    else if (wave == 1) l44_face_link<C, 1, PI>(uf, a.U, nbr, b, j);
-    else if (wave == 2) l44_face_link<C, 2, PI>(uf, a.U, nbr, b, j);
-    else l44_face_link<C, 3, PI>(uf, a.U, nbr, b, j);
+    if (wave == 0) l44_face_link<C, 0>(uf, a.U, nbr, b, j);
+    else if (wave == 1) l44_face_link<C, 1>(uf, a.U, nbr, b, j);
+    else if (wave == 2) l44_face_link<C, 2>(uf, a.U, nbr, b, j);
+    else l44_face_link<C, 3>(uf, a.U, nbr, b, j);
   };
   if constexpr (HOLD) {
 #pragma unroll

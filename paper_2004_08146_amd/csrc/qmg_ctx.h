@@ -30,7 +30,6 @@ struct Tune {
   int dslash_xcd_remap = 1;                      // XCD-aware mapping of work-groups to blocks
   int force_variant = -1;                        // >= 0: use this stencil variant (tuning, tests)
   int sap_variant = 2;  // SAP: 0 generic kernel; 1 gathering 4^4 kernel (FP32 / BF16); 2 halo-field 4^4 kernel
-  int coarse_rhs_tile = 4;                       // right-hand sides per coarse-apply work-group
   int coarse_mfma = 1;                           // MFMA coarse apply for many right-hand sides
   int restrict_mfma_min_rhs = 4;                 // restriction on MFMA from this many rhs (1000: never)
   int ds_order = 0;  // stencil work order: 0 blocks in lexicographic order, t > 0 tiles of kTileShapes[t] blocks
@@ -51,7 +50,7 @@ struct Level3 {
   const int* keep = nullptr;   // [nb][9] 1 where stencil entry d of the site stays in its aggregate
   const int* nbr3 = nullptr;   // [n3][8] level-3 neighbours: 2 mu forward, 2 mu + 1 backward
   void* P2[2] = {nullptr, nullptr};  // F64, F32: [n3][2][bs2 * ntv][ntv2]
-  void* D3[2] = {nullptr, nullptr};  // F64, F32: [n3][9][2 ntv2][2 ntv2] (transposed blocks)
+  void* D3[2] = {nullptr, nullptr};  // F64, F32: [n3][5][2 ntv2][2 ntv2] (self and forward blocks, transposed)
 };
 
 struct qmg_ctx {
@@ -169,16 +168,12 @@ int dot_chunks(int64_t n);
 hipError_t launch_dot_partials(int p, const void* V, int64_t vstride, int J, const void* w, int64_t n, int64_t stride,
                                int nrhs, double* partial, hipStream_t s, int with_self = 0);
 // the update and the chunk sums of its squared norm: partial[(k*dot_chunks(n) + chunk)*2 ..];
-// with sig ([nrhs][ldsig] on the device) w is first scaled by the power of two below sig_aj (0 for 0)
+// with sig ([nrhs][ldsig] on the device) w is first scaled by the power of two below sig_aj (0 for 0);
+// with copy (p == QMG_F64 only) the result is also written there in copy_prec (FP32 or BF16),
+// bit for bit what launch_convert would write
 hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                                 int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy = nullptr,
                                 int copy_prec = QMG_F64, const double* sig = nullptr, int ldsig = 0, int aj = 0);
-// w_k += sum_j coef[k*J + j] V_j,k and norms[2k] = ||w_k||^2 of the result; with copy
-// (p == QMG_F64 only) the result is also written there in copy_prec (FP32 or BF16),
-// bit for bit what launch_convert would write
-hipError_t launch_axpy_norm(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
-                            int64_t stride, int nrhs, double* norms, double* partial, hipStream_t s,
-                            void* copy = nullptr, int copy_prec = QMG_F64);
 // One Gram-Schmidt pass on a basis v_j = sig_j W_j (sig: [nrhs][ldsig] on the device): the
 // projections dots (as launch_multidot) with the update's coefficients -scale sig_j^2 dots, and
 // the update of scale w with (squared norm, scale) of its results in norms and their sig as

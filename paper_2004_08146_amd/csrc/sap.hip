@@ -506,7 +506,8 @@ __device__ __forceinline__ void slot_sum3(float (&v)[3], float* red, int slot) {
   }
 }
 
-template <typename S, bool CLOVER, int NS, bool QF>
+constexpr int NS = 2;  // right-hand sides in flight in a work-group
+template <typename S, bool CLOVER, bool QF>
 __global__ __launch_bounds__(256 * NS) void k_sap44(SapArgs<S> a) {
   using P = typename PT<S>::stor;
   __shared__ cpx<float> Ul[36 * 256];
@@ -661,11 +662,11 @@ void launch_s(const qmg_ctx* c, int p, void* x, const void* f, const double* tau
     if (fits44(c, p) && c->tune.sap_variant >= 1) {
       dim3 grid((unsigned)a.nblk);
       if (qf) {
-        if (c->clover) hipLaunchKernelGGL((k_sap44<S, true, 2, true>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((k_sap44<S, false, 2, true>), grid, dim3(512), 0, s, a);
+        if (c->clover) hipLaunchKernelGGL((k_sap44<S, true, true>), grid, dim3(256 * NS), 0, s, a);
+        else hipLaunchKernelGGL((k_sap44<S, false, true>), grid, dim3(256 * NS), 0, s, a);
       } else {
-        if (c->clover) hipLaunchKernelGGL((k_sap44<S, true, 2, false>), grid, dim3(512), 0, s, a);
-        else hipLaunchKernelGGL((k_sap44<S, false, 2, false>), grid, dim3(512), 0, s, a);
+        if (c->clover) hipLaunchKernelGGL((k_sap44<S, true, false>), grid, dim3(256 * NS), 0, s, a);
+        else hipLaunchKernelGGL((k_sap44<S, false, false>), grid, dim3(256 * NS), 0, s, a);
       }
       return;
     }

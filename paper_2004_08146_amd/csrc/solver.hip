@@ -475,9 +475,10 @@ static qmg_status vcycle_body(qmg_ctx* c, void* z, const void* r, const double* 
 // ------------------------------------------------------------------ FGMRES --
 // Columns that have converged when a restart cycle ends are dropped from the
 // batch: the next cycles run on the unconverged columns only (gathered to the
-// front of library buffers; every column is an independent system, so its
-// arithmetic does not depend on which others share the batch), and each
-// column's x is written back to the caller's x when it leaves the batch.
+// front of library buffers), and each column's x is written back to the
+// caller's x when it leaves the batch.  Every column is an independent system;
+// the batch's size only picks kernels, which in the transfers and the coarse
+// products changes the order of sums (the stencil and SAP return the same bits).
 qmg_status solver_fgmres(qmg_ctx* c, void* x, const void* b, const double* tau, int nrhs, const qmg_params* prm,
                          qmg_stats* stats, hipStream_t s) {
   auto t0 = std::chrono::steady_clock::now();
