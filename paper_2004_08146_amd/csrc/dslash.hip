@@ -232,8 +232,28 @@ __device__ __forceinline__ Half<C> udagmul44(const Link<C>& U, const Half<C>& h)
     }
   return o;
 }
-// w = one Hermitian 6x6 block (ld(k): its k-th stored entry) times v
-template <typename C, typename F>
+// the sum of the two hops of direction MU from their colour-rotated half spinors: both
+// kernels add a direction's two hops first, then the directions in order
+template <typename C, int MU>
+__device__ __forceinline__ Spinor<C> pair44(const Half<C>& f, const Half<C>& b) {
+  Spinor<C> p;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    p.s[0][c] = f.h[0][c] + b.h[0][c];
+    p.s[1][c] = f.h[1][c] + b.h[1][c];
+    const cpx<C> d0 = f.h[0][c] - b.h[0][c], d1 = f.h[1][c] - b.h[1][c];
+    if constexpr (MU == 0) p.s[2][c] = d0, p.s[3][c] = d1;
+    else if constexpr (MU == 1) p.s[2][c] = tmi(d1), p.s[3][c] = tmi(d0);
+    else if constexpr (MU == 2) p.s[2][c] = -d1, p.s[3][c] = d0;
+    else p.s[2][c] = tmi(d0), p.s[3][c] = ti(d1);
+  }
+  return p;
+}
+// w = one Hermitian 6x6 block (ld(k): its k-th stored entry) times v.  The diagonal is fused
+// with a row's first product; MUL: written as a product of its own, which the compiler fuses
+// alike but orders the loads otherwise (64x32^3, 16 rhs, bf16 2.24 ms against 2.32 without;
+// FP32 3.33 against 3.31, FP64 4 rhs 1.725 against 1.713)
+template <typename C, bool MUL, typename F>
 __device__ __forceinline__ void block44(cpx<C> (&w)[6], const cpx<C> (&v)[6], F&& ld) {
   C d[6];
 #pragma unroll
@@ -241,6 +261,7 @@ __device__ __forceinline__ void block44(cpx<C> (&w)[6], const cpx<C> (&v)[6], F&
     const cpx<C> t = ld(k);
     d[2 * k] = t.re;
     d[2 * k + 1] = t.im;
+    if constexpr (MUL) w[2 * k] = t.re * v[2 * k], w[2 * k + 1] = t.im * v[2 * k + 1];
   }
   int k = 3;
 #pragma unroll
@@ -249,16 +270,16 @@ __device__ __forceinline__ void block44(cpx<C> (&w)[6], const cpx<C> (&v)[6], F&
     for (int j = 0; j < i; ++j) {
       const cpx<C> a = ld(k), p = mul44(a, v[j]), q = mul_conj44(a, v[i]);
       ++k;
-      // the diagonal enters with a row's first product
-      w[i] = j == 0 ? cpx<C>{fmar(d[i], v[i].re, p.re), fmar(d[i], v[i].im, p.im)} : w[i] + p;
-      w[j] = i == 1 ? cpx<C>{fmar(d[j], v[j].re, q.re), fmar(d[j], v[j].im, q.im)} : w[j] + q;
+      w[i] = !MUL && j == 0 ? cpx<C>{fmar(d[i], v[i].re, p.re), fmar(d[i], v[i].im, p.im)} : w[i] + p;
+      w[j] = !MUL && i == 1 ? cpx<C>{fmar(d[j], v[j].re, q.re), fmar(d[j], v[j].im, q.im)} : w[j] + q;
     }
 }
 // (D - tau Gamma5) psi (MODE 0) or (Gamma5 D - tau) psi at one entry of chirality H: o the
-// diagonal part, hops the sum of the hops
-template <typename C, int MODE, int H>
-__device__ __forceinline__ cpx<C> tail44(cpx<C> o, cpx<C> hops, cpx<C> psi, C tau) {
-  const cpx<C> v = {fmar(C(-0.5), hops.re, o.re), fmar(C(-0.5), hops.im, o.im)};
+// clover part, hops the sum of the hops (half of it is exact)
+template <typename C, bool CLOVER, int MODE, int H>
+__device__ __forceinline__ cpx<C> tail44(cpx<C> o, C mass4, cpx<C> hops, cpx<C> psi, C tau) {
+  const cpx<C> v = CLOVER ? cpx<C>{fmar(C(-0.5), hops.re, o.re), fmar(C(-0.5), hops.im, o.im)}
+                          : cpx<C>{fmar(mass4, psi.re, C(-0.5) * hops.re), fmar(mass4, psi.im, C(-0.5) * hops.im)};
   if (H == 0) return {fmar(-tau, psi.re, v.re), fmar(-tau, psi.im, v.im)};
   if (MODE == 0) return {fmar(tau, psi.re, v.re), fmar(tau, psi.im, v.im)};
   return {fmar(-tau, psi.re, -v.re), fmar(-tau, psi.im, -v.im)};
@@ -273,7 +294,7 @@ __device__ __forceinline__ Spinor<C> diag44(const P* D, uint32_t b, uint32_t l, 
     cpx<C> v[6], w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) v[i] = p.s[2 * h + i / 3][i % 3];
-    block44(w, v, [&](int k) {
+    block44<C, std::is_same<P, uint32_t>::value>(w, v, [&](int k) {
       const auto d = cv(ldo(D, ((b * 36u + (uint32_t)(18 * h + k)) << 8) + l));
       return cpx<C>{C(d.re), C(d.im)};
     });
@@ -348,10 +369,16 @@ __device__ __forceinline__ void l44_dir(Spinor<C>& acc, const Spinor<C>& psi, co
   Half<C> h, w;
 #pragma unroll
   for (int i = 0; i < 6; ++i) h.h[i / 3][i % 3] = hb[i * 256 + lf];
-  accum_recon(acc, umul44(u, h), MU, true);
+  h = umul44(u, h);
 #pragma unroll
   for (int i = 0; i < 6; ++i) w.h[i / 3][i % 3] = wb[i * 256 + lb];
-  accum_recon(acc, w, MU, false);
+  const Spinor<C> p = pair44<C, MU>(h, w);
+  if constexpr (MU == 0) {
+    acc = p;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 12; ++i) acc.s[i / 3][i % 3] = acc.s[i / 3][i % 3] + p.s[i / 3][i % 3];
+  }
   pin(acc);
 }
 
@@ -396,10 +423,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     else if (wave == 2) l44_face<C, 2>(fh, fw, in, uf, nbr, b, lane);
     else l44_face<C, 3>(fh, fw, in, uf, nbr, b, lane);
     Spinor<C> acc;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
     cpx<C>*h0 = buf, *w0 = buf + 6 * 256, *h1 = TWO ? buf + 12 * 256 : h0, *w1 = TWO ? buf + 18 * 256 : w0;
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -414,22 +437,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
     }
     Spinor<C> o;
-    if constexpr (CLOVER) {
-      o = diag44<C>(a.diag, b, l, psi);
-    } else {
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) o.s[s][c] = C(a.mass4) * psi.s[s][c];
-    }
-    const C tau = C(a.tau[k]);
+    if constexpr (CLOVER) o = diag44<C>(a.diag, b, l, psi);
+    const C tau = C(a.tau[k]), mass4 = C(a.mass4);
     P* out = a.out + (size_t)k * a.fstride;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int c = 0; c < 3; ++c)
-        o.s[s][c] = s < 2 ? tail44<C, MODE, 0>(o.s[s][c], acc.s[s][c], psi.s[s][c], tau)
-                          : tail44<C, MODE, 1>(o.s[s][c], acc.s[s][c], psi.s[s][c], tau);
+        o.s[s][c] = s < 2 ? tail44<C, CLOVER, MODE, 0>(o.s[s][c], mass4, acc.s[s][c], psi.s[s][c], tau)
+                          : tail44<C, CLOVER, MODE, 1>(o.s[s][c], mass4, acc.s[s][c], psi.s[s][c], tau);
     if (a.nt_out) {
 #pragma unroll
       for (int i = 0; i < 12; ++i) sto_nt(out, ((b * 12u + (uint32_t)i) << 8) + l, vc(o.s[i / 3][i % 3], (P*)nullptr));
@@ -443,43 +459,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // ---- 4^4 blocks, few of them: a work-group is a quarter of a block (64 sites), wave w
 // takes the two hops of direction w, so that a site's 8 hops are one round of loads instead
-// of a chain of them, and there are four times as many work-groups.  The half spinors of all
-// hops meet in LDS and are added in the order of k_dslash44l, so that a column's result does
-// not depend, in rounding, on the batch by which the launch picks between the two.
+// of a chain of them, and there are four times as many work-groups.
 template <typename C, int MU, typename PI, typename P>
-__device__ __forceinline__ void s44_pair(cpx<C> (*part)[6][64], const PI* in, const P* U, const int* nbr, uint32_t b,
-                                         uint32_t l, uint32_t lane) {
+__device__ __forceinline__ Spinor<C> s44_pair(const PI* in, const P* U, const int* nbr, uint32_t b, uint32_t l) {
   constexpr int SH = kL44Sh[MU];
   const uint32_t lc = (l >> SH) & 3u;
   const uint32_t bf = lc == 3u ? (uint32_t)nbr[b * 8 + 2 * MU] : b, bb = lc == 0u ? (uint32_t)nbr[b * 8 + 2 * MU + 1] : b;
   const uint32_t lf = lc == 3u ? l - (3u << SH) : l + (1u << SH), lb = lc == 0u ? l + (3u << SH) : l - (1u << SH);
   const Spinor<C> pf = ld_spinor44<C>(in, bf, lf), pb = ld_spinor44<C>(in, bb, lb);
   const Link<C> uf = ld_link44<C>(U, b, MU, l), ub = ld_link44<C>(U, bb, MU, lb);
-  const Half<C> hf = umul44(uf, project(pf, MU, true)), hb = udagmul44(ub, project(pb, MU, false));
-#pragma unroll
-  for (int c = 0; c < 6; ++c) {
-    part[2 * MU][c][lane] = hf.h[c / 3][c % 3];
-    part[2 * MU + 1][c][lane] = hb.h[c / 3][c % 3];
-  }
-}
-// the sum of the eight hops, as l44_dir forms it
-template <typename C, int MU>
-__device__ __forceinline__ void s44_add(Spinor<C>& acc, const cpx<C> (*part)[6][64], uint32_t lane) {
-  Half<C> hf, hb;
-#pragma unroll
-  for (int c = 0; c < 6; ++c) {
-    hf.h[c / 3][c % 3] = part[2 * MU][c][lane];
-    hb.h[c / 3][c % 3] = part[2 * MU + 1][c][lane];
-  }
-  accum_recon(acc, hf, MU, true);
-  accum_recon(acc, hb, MU, false);
+  return pair44<C, MU>(umul44(uf, project(pf, MU, true)), udagmul44(ub, project(pb, MU, false)));
 }
 
 template <typename S, bool CLOVER, int MODE, typename SI>
 __global__ __launch_bounds__(256) void k_dslash44s(DsArgs<S, SI> a) {
   using C = typename PT<S>::real;
   using P = typename PT<S>::stor;
-  __shared__ cpx<C> part[8][6][64];
+  __shared__ cpx<C> part[4][12][64];
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   const uint32_t l = ((blockIdx.x & 3u) << 6) | lane, i = blockIdx.x >> 2;
   const uint32_t b = i / (uint32_t)a.nrhs, k = i - b * (uint32_t)a.nrhs;
@@ -499,35 +495,26 @@ __global__ __launch_bounds__(256) void k_dslash44s(DsArgs<S, SI> a) {
         dg[c] = cpx<C>{C(t.re), C(t.im)};
       }
   }
-  if (wave == 0) s44_pair<C, 0>(part, in, a.U, a.g.nbr, b, l, lane);
-  else if (wave == 1) s44_pair<C, 1>(part, in, a.U, a.g.nbr, b, l, lane);
-  else if (wave == 2) s44_pair<C, 2>(part, in, a.U, a.g.nbr, b, l, lane);
-  else s44_pair<C, 3>(part, in, a.U, a.g.nbr, b, l, lane);
+  Spinor<C> acc;
+  if (wave == 0) acc = s44_pair<C, 0>(in, a.U, a.g.nbr, b, l);
+  else if (wave == 1) acc = s44_pair<C, 1>(in, a.U, a.g.nbr, b, l);
+  else if (wave == 2) acc = s44_pair<C, 2>(in, a.U, a.g.nbr, b, l);
+  else acc = s44_pair<C, 3>(in, a.U, a.g.nbr, b, l);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) part[wave][c][lane] = acc.s[c / 3][c % 3];
   __syncthreads();
-  const C tau = C(a.tau[k]);
+  const C tau = C(a.tau[k]), mass4 = C(a.mass4);
   typename PT<S>::stor* out = a.out + (size_t)k * a.fstride;
   auto finish = [&](auto hc) {
     constexpr int H = decltype(hc)::value;
-    Spinor<C> acc;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc.s[s][c] = czero<C>();
-    s44_add<C, 0>(acc, part, lane);
-    s44_add<C, 1>(acc, part, lane);
-    s44_add<C, 2>(acc, part, lane);
-    s44_add<C, 3>(acc, part, lane);
     cpx<C> w[6];
-    if constexpr (CLOVER) {
-      block44(w, v, [&](int q) { return dg[q]; });
-    } else {
-#pragma unroll
-      for (int c = 0; c < 6; ++c) w[c] = C(a.mass4) * v[c];
-    }
+    if constexpr (CLOVER) block44<C, std::is_same<P, uint32_t>::value>(w, v, [&](int q) { return dg[q]; });
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-      const cpx<C> r = tail44<C, MODE, H>(w[c], acc.s[2 * H + c / 3][c % 3], v[c], tau);
-      sto(out, ((b * 12u + 6u * H + (uint32_t)c) << 8) + l, vc(r, (P*)nullptr));
+      const int at = 6 * H + c;
+      const cpx<C> hops = ((part[0][at][lane] + part[1][at][lane]) + part[2][at][lane]) + part[3][at][lane];
+      const cpx<C> r = tail44<C, CLOVER, MODE, H>(w[c], mass4, hops, v[c], tau);
+      sto(out, ((b * 12u + (uint32_t)at) << 8) + l, vc(r, (P*)nullptr));
     }
   };
   if (wave == 0) finish(std::integral_constant<int, 0>{});
