@@ -80,8 +80,9 @@ __global__ __launch_bounds__(kDotWG) void k_dot_stage1(double* partial, const ty
 
 // The loads of eight entries of one or two basis vectors are in flight together (8 coarse
 // vectors of 32^4, FP32, 10 basis vectors: 32 -> 23 us).
-// w_k = scale_k w_k + sum_j coef[k*J+j] V_j,k over one chunk, and partial[k][chunk] =
-// ||new w_k||^2 there; scale_k = basis_scale(sig[k*ldsig + aj]), or 1 without sig.
+// w_k = scale_k (w_k + sum_j coef[k*J+j] V_j,k) over one chunk, and partial[k][chunk] =
+// ||new w_k||^2 there; scale_k = basis_scale(sig[k*ldsig + aj]), or 1 without sig.  (The
+// scale on w itself made the basis wait for w: 16^4 FP64 solve 11.38 -> 11.47 ms.)
 // With a copy type C (FP32 or BF16 storage), the new w is also written to cp in
 // that storage, rounded through FP32 exactly as the conversion kernel rounds it.
 template <typename S, typename C = void>
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kDotWG) void k_axpy_norm(typename PT<S>::stor* w, c
     };
     cpx<double> v[kDotPerThread];
 #pragma unroll
-    for (int t = 0; t < kDotPerThread; ++t) v[t] = al * get(wk, t);
+    for (int t = 0; t < kDotPerThread; ++t) v[t] = get(wk, t);
 #pragma unroll 2
     for (int j = 0; j < J; ++j) {
       const cpx<double> c = {coef[((int64_t)k * J + j) * 2], coef[((int64_t)k * J + j) * 2 + 1]};
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(kDotWG) void k_axpy_norm(typename PT<S>::stor* w, c
     for (int t = 0; t < kDotPerThread; ++t) {
       const int64_t i = i0 + (int64_t)t * kDotWG;
       if (kFull || i < n) {
-        const cpx<R> vr = {R(v[t].re), R(v[t].im)};
+        const cpx<R> vr = {R(al * v[t].re), R(al * v[t].im)};
         const auto st = vc(vr, (typename PT<S>::stor*)nullptr);
         wk[i] = st;
         if constexpr (!std::is_void<C>::value) stcv(cp + k * stride, i, cpx<float>{float(vr.re), float(vr.im)});
@@ -152,15 +153,12 @@ __global__ __launch_bounds__(256) void k_dot_stage2(double* dots, const double* 
 }
 
 // As k_dot_stage2 for the projections of one Gram-Schmidt pass: dots as it, and for j < J
-// also the update's coefficients coef[k*J + j] = -scale sig_j^2 dots (basis v_j = sig_j W_j),
-// scale = basis_scale(sig_aj), or 1 for aj < 0
+// also the update's coefficients coef[k*J + j] = -sig_j^2 dots (basis v_j = sig_j W_j)
 __global__ __launch_bounds__(256) void k_project_stage2(double* dots, double* coef, const double* partial,
-                                                        const double* sig, int ldsig, int aj, int J, int JT,
-                                                        int nchunk) {
+                                                        const double* sig, int ldsig, int J, int JT, int nchunk) {
   __shared__ double red[2 * 4];
   const int j = blockIdx.x, k = blockIdx.y;
-  const double* sg = sig + (int64_t)k * ldsig;
-  const double s = sg[min(j, J - 1)], scale = aj < 0 ? 1.0 : basis_scale(sg[aj]);  // before the sums, not after
+  const double s = sig[(int64_t)k * ldsig + min(j, J - 1)];  // before the sums, not after
   const double* p = partial + ((int64_t)k * JT + j) * nchunk * 2;
   double acc[2] = {0.0, 0.0};
   for (int c = threadIdx.x; c < nchunk; c += blockDim.x) {
@@ -172,7 +170,7 @@ __global__ __launch_bounds__(256) void k_project_stage2(double* dots, double* co
     dots[((int64_t)k * JT + j) * 2] = acc[0];
     dots[((int64_t)k * JT + j) * 2 + 1] = acc[1];
     if (j < J) {
-      const double s2 = -s * s * scale;
+      const double s2 = -s * s;
       coef[((int64_t)k * J + j) * 2] = s2 * acc[0];
       coef[((int64_t)k * J + j) * 2 + 1] = s2 * acc[1];
     }
@@ -329,7 +327,7 @@ hipError_t launch_multidot_shared(int p, double* dots, const void* V, int64_t vs
   return hipGetLastError();
 }
 
-// w_k = scale_k w_k + sum_j coef V_j,k; partial[k][chunk] = ||w_k||^2 over the chunk afterwards
+// w_k = scale_k (w_k + sum_j coef V_j,k); partial[k][chunk] = ||w_k||^2 over the chunk afterwards
 hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                                 int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy, int copy_prec,
                                 const double* sig, int ldsig, int aj) {
@@ -355,11 +353,11 @@ hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, 
 
 hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
                           int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
-                          hipStream_t s, int with_self, int aj) {
+                          hipStream_t s, int with_self) {
   const hipError_t e = launch_dot_partials(p, V, vstride, J, w, n, stride, nrhs, partial, s, with_self);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_project_stage2, dim3(J + with_self, nrhs), dim3(256), 0, s, dots, coef, partial, sig, ldsig, aj,
-                     J, J + with_self, dot_chunks(n));
+  hipLaunchKernelGGL(k_project_stage2, dim3(J + with_self, nrhs), dim3(256), 0, s, dots, coef, partial, sig, ldsig, J,
+                     J + with_self, dot_chunks(n));
   return hipGetLastError();
 }
 

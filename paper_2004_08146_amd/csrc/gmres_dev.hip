@@ -9,7 +9,7 @@
 // vector): each product is orthogonalised in place in the next basis slot, so
 // no scaling pass is needed, and the last step, whose new vector is never used,
 // takes ||w_new||^2 = ||w||^2 - sum_i |v_i^H w|^2 from its dot pass instead of
-// an update pass.  The update also gives w a power of two near sig_j, so that
+// an update pass.  The update also gives its result a power of two near sig_j, so that
 // ||W_{j+1}|| stays near h_{j+1,j} for any number of steps.
 // One thread per right-hand side; the rotations follow the same convention as
 // the host solver: [[c, s], [-conj(s), c]] [a; b] = [r; 0], c real.
@@ -109,8 +109,7 @@ __device__ void gm_close(const GmState& st, int k, int j, double norm2w, double 
 }
 
 // One classical Gram-Schmidt pass for w = A W_j, d_i = W_i^H w summed here from the chunk
-// sums: H[i][j] = sig_i sig_j d_i, coef_i = -scale sig_i^2 d_i (w -= (v_i^H w) v_i, times
-// the scale of sig_j).
+// sums: H[i][j] = sig_i sig_j d_i, coef_i = -sig_i^2 d_i (w -= (v_i^H w) v_i).
 // last: the sums also hold ||w||^2 (at index J); the squared norm of the projected w,
 // ||w||^2 - sum_i sig_i^2 |d_i|^2, takes the place of the update pass and the column is
 // closed at once.  One work-group per right-hand side, which also closes the column where
@@ -125,10 +124,9 @@ __global__ __launch_bounds__(kGmWG) void k_gm_coef(GmState st, const double* par
   gm_sums(partial + (int64_t)k * ld * nchunk * 2, ld, nchunk, d);
   const double* sg = st.sig + (int64_t)k * (m + 1);
   if (!last) {
-    const double scale = basis_scale(sg[j]);
     for (int i = threadIdx.x; i < J; i += kGmWG) {
       const cpx<double> di = {d[i][0], d[i][1]};
-      stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * scale * di);
+      stz(coef, (int64_t)k * J + i, -(sg[i] * sg[i]) * di);
       stz(st.H, (int64_t)k * (m + 1) * m + (int64_t)i * m + j, (sg[i] * sg[j]) * di);
     }
   } else if (threadIdx.x == 0) {  // scales d in place: no other thread reads it here

@@ -168,19 +168,19 @@ int dot_chunks(int64_t n);
 hipError_t launch_dot_partials(int p, const void* V, int64_t vstride, int J, const void* w, int64_t n, int64_t stride,
                                int nrhs, double* partial, hipStream_t s, int with_self = 0);
 // the update and the chunk sums of its squared norm: partial[(k*dot_chunks(n) + chunk)*2 ..];
-// with sig ([nrhs][ldsig] on the device) w is first scaled by the power of two below sig_aj (0 for 0);
+// with sig ([nrhs][ldsig] on the device) the result is scaled by the power of two below sig_aj (0 for 0);
 // with copy (p == QMG_F64 only) the result is also written there in copy_prec (FP32 or BF16),
 // bit for bit what launch_convert would write
 hipError_t launch_axpy_partials(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                                 int64_t stride, int nrhs, double* partial, hipStream_t s, void* copy = nullptr,
                                 int copy_prec = QMG_F64, const double* sig = nullptr, int ldsig = 0, int aj = 0);
 // One Gram-Schmidt pass on a basis v_j = sig_j W_j (sig: [nrhs][ldsig] on the device): the
-// projections dots (as launch_multidot) with the update's coefficients -scale sig_j^2 dots, and
-// the update of scale w with (squared norm, scale) of its results in norms and their sig as
-// basis vector `at`; scale: the power of two below sig_aj (0 for 0), 1 for aj < 0
+// projections dots (as launch_multidot) with the update's coefficients -sig_j^2 dots, and
+// the update, times scale, with (squared norm, scale) of its results in norms and their sig
+// as basis vector `at`; scale: the power of two below sig_aj (0 for 0), 1 for aj < 0
 hipError_t launch_project(int p, double* dots, double* coef, const double* sig, int ldsig, const void* V,
                           int64_t vstride, int J, const void* w, int64_t n, int64_t stride, int nrhs, double* partial,
-                          hipStream_t s, int with_self, int aj);
+                          hipStream_t s, int with_self);
 hipError_t launch_axpy_sig(int p, void* w, const void* V, int64_t vstride, int J, const double* coef, int64_t n,
                            int64_t stride, int nrhs, double* norms, double* sig, int ldsig, int aj, int at,
                            double* partial, hipStream_t s, void* copy = nullptr, int copy_prec = QMG_F64);

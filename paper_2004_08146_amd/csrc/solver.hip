@@ -167,7 +167,7 @@ struct Space {
   // cycle anyway.  The new norm comes out of the update pass.
   // The basis is stored unnormalised, v_i = sig_i W_i, sig ([nrhs][j + 2]) here and in
   // dsig ([nrhs][ldsig]) on the device: the projections use sig_i (W_i^H w) and the update
-  // subtracts sig_i^2 (W_i^H w) W_i, after w took a power of two near sig_j, without which
+  // subtracts sig_i^2 (W_i^H w) W_i; the result takes a power of two near sig_j, without which
   // ||W_{j+1}|| would be the product of all h_{i+1,i} and leave the storage type's range.
   // The update's coefficients are formed on the device and projections and norm are read
   // together, so a pass waits once.  Fills sig_{j+1} in both places.
@@ -189,7 +189,7 @@ struct Space {
     std::vector<double> before(nrhs), after(nrhs), unscale(nrhs);  // unscale: 1 / scale (0 for 0)
     for (int pass = 0; pass < 2; ++pass) {
       const int self = pass == 0 ? 1 : 0, aj = pass == 0 ? j : -1;
-      hipError_t e = launch_project(p, d, dc, dsig, ldsig, V, vstride(), J, w, n, n, nrhs, part, s, self, aj);
+      hipError_t e = launch_project(p, d, dc, dsig, ldsig, V, vstride(), J, w, n, n, nrhs, part, s, self);
       if (e == hipSuccess)
         e = launch_axpy_sig(p, w, V, vstride(), J, dc, n, n, nrhs, d + nd, dsig, ldsig, aj, J, part, s, copy, copy_prec);
       if (e == hipSuccess) e = hipMemcpyAsync(hd, d, sizeof(double) * nres, hipMemcpyDeviceToHost, s);
